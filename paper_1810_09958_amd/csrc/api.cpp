@@ -431,6 +431,105 @@ bool pack_b_needed(int trans_b, int64_t N, int64_t K, int ab_type, const void* B
     return ((uintptr_t)B & 15) || (ldb * es) % 16 || (trans_b ? K : N) % E;
 }
 
+// bf16 products whose 128x128 tiles leave CUs idle run on the LDS-ring kernel
+// (gemm_ring.hpp), any layout.  Tile and K split by a cost model of that
+// kernel, fitted to a sweep on MI355X: a 64-deep K tile takes 0.47 us for a
+// 128x128 workgroup (one per CU) and 0.21 us for a 64x64 one alone on its CU
+// (0.20 each when two share it); further rounds cost 2.5 / 1.5 us of start and
+// end each; a split into S slices 4 + 1.5 S us (128x128) or 1 + S / 2 (64x64).
+// Measured, bf16, us (ring / the plans it replaces; at 128x128 grids of at
+// least one tile per CU the three-stage ring of gemm_dma.hpp is as fast or
+// faster: 2048x3072x1024 NT 22 / 17.5, 2048^3 23 / 23):
+//   3072x1024x2048 TN 18.1 / 47.6, 2608x1032x4472 TN 37 / 77, 1024^3 NN 7.7 / 16.9,
+//   648x1520x3096 NT 20 / 28, 4968x128x2064 NN 12.3 / 22.5, 512x512x4096 NN 11.9 / 21.9.
+// ISAM_GEMM_CONFIG ring=0 switches it off, ring=1 / ring=2 force 128x128 / 64x64
+// tiles and rs=<n> the K slices; settings of the other kernels also switch it off.
+RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool may_split) {
+    RingPlan none{0, 1};
+    if (M <= 0 || N <= 0 || K <= 0) return none;
+    const int64_t nk = cdiv(K, 64);
+    int force = 0, force_s = 0;
+    if (const char* env = getenv("ISAM_GEMM_CONFIG")) {
+        for (const char* k : {"tile=", "splits=", "dma=", "dmaw=", "sk=1", "stream=1", "ring=0"})
+            if (strstr(env, k)) return none;
+        const char* q;
+        if ((q = strstr(env, "ring="))) force = std::min(2, atoi(q + 5));
+        if ((q = strstr(env, "rs="))) force_s = atoi(q + 3);
+    }
+    if (!force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
+    RingPlan best = none;
+    double best_us = 0;
+    for (int ring = 1; ring <= 2; ++ring) {
+        if (force && ring != force) continue;
+        int bm, bn;
+        gemm_ring_dims(ring, &bm, &bn);
+        const int64_t tiles = batch * cdiv(M, bm) * cdiv(N, bn);
+        const int64_t most = may_split ? std::max<int64_t>(1, std::min<int64_t>(force ? 255 : 8, nk / (force ? 1 : 4))) : 1;
+        for (int64_t sp = 1; sp <= most; ++sp) {
+            if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
+            const int64_t iters = cdiv(nk, sp), per_cu = cdiv(tiles * cdiv(nk, iters), cus);
+            const double us = ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
+                                        : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
+                                              (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);
+            if (!best.ring || us < best_us) {
+                best = RingPlan{ring, (int)sp};
+                best_us = us;
+            }
+        }
+    }
+    return best;
+}
+
+// Operand copies (pack.hip) that let a product with unaligned rows take the
+// ring kernel: each operand that needs it copied row by row into rows
+// of a multiple of 8 values (zeros past the row's end: K positions beyond K
+// add exact zeros, columns beyond M or N are not stored).
+struct RingPack {
+    bool a = false, b = false;
+    int64_t a_cols = 0, b_cols = 0;   // packed row lengths
+    size_t a_bytes = 0, b_bytes = 0;  // each a multiple of 256
+};
+RingPack ring_pack(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a, bool need_b) {
+    RingPack k;
+    auto al = [](int64_t v) { return (size_t)((v + 255) & ~(int64_t)255); };
+    // whole 128-byte lines where that adds at most an eighth: a copied row
+    // segment that straddles lines costs the copies up to half of their rate
+    auto cols = [](int64_t v) { return (cdiv(v, 64) * 64 - v) * 8 <= v ? cdiv(v, 64) * 64 : cdiv(v, 8) * 8; };
+    k.a = need_a;
+    k.b = need_b;
+    if (need_a) {
+        k.a_cols = cols(trans_a ? M : K);
+        k.a_bytes = al((trans_a ? K : M) * k.a_cols * 2);
+    }
+    if (need_b) {
+        k.b_cols = cols(trans_b ? K : N);
+        k.b_bytes = al((trans_b ? N : K) * k.b_cols * 2);
+    }
+    return k;
+}
+// The copies are one more launch (about 3 us per call).  The element-wise
+// kernel it saves walks K one tile at a time and transposes in registers where
+// an operand's rows run along M or N: 89x170x800 TN 28 us against 10 and
+// 326x468x1573 NN 26 against 13, but 298x1281x100 NN 8.8 against 10 and, with
+// both operands' rows along K (NT), 300^3 7.3 against 10, 2021x271x374 7.7 against
+// 10.2, 700x700x701 12.3 against 10.9.
+bool ring_pack_pays(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const RingPack& k) {
+    const char* env = getenv("ISAM_GEMM_CONFIG");
+    if (env && strstr(env, "pack=0")) return false;
+    const bool pays = trans_a || !trans_b ? K > 128 && M * N * K >= (int64_t(1) << 20) : M * N * K >= (int64_t(1) << 28);
+    return pays && (int64_t)k.a_bytes <= kMaxExtent && (int64_t)k.b_bytes <= kMaxExtent;
+}
+
+// Whether a plan of plan_gemm keeps its special kernel (skinny, narrow, small or
+// streaming) for these operands instead of the ring kernel.
+bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool vec,
+                    bool a_rows_aligned, int cus) {
+    if (p.skinny == 4) return !trans_a && !trans_b && a_rows_aligned;
+    if (p.skinny) return vec && !trans_a && !trans_b;
+    if (p.small) return vec && !trans_a;
+    return vec && !trans_a && !trans_b && K <= kStreamMaxK && N <= 256 && N % 4 == 0 && cdiv(M, 32) >= cus;
+}
+
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
                             const void* A, int64_t lda, const void* B, int64_t ldb, int accumulate,
                             int c_type, const void* C, int64_t ldc, const char* who) {
@@ -509,6 +608,66 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
             if (e != hipSuccess) return hip_fail(e, who);
             return run_gemm(0, trans_b, M, N, 6 * k.Kp, kBF16, As, 6 * k.Kp, Bs, trans_b ? 6 * k.Kp : N, accumulate,
                             c_type, C, ldc, bias, ws + split_bytes, workspace_bytes - split_bytes, stream, who);
+        }
+    }
+    if (ab_type == kBF16 && K > 0) {
+        const int cus = device_cus();
+        const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
+        RingPlan r = plan_ring(M, N, K, batch, cus, batch == 1);
+        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, p.vec && batch == 1, !((uintptr_t)A & 15) && lda % 8 == 0, cus)) {
+            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, need_a, need_b);
+            const size_t pack_bytes = k.a_bytes + k.b_bytes;
+            char* ws = static_cast<char*>(workspace);
+            const bool ws_ok = ws && ((uintptr_t)ws & 255) == 0 && batch == 1;
+            const bool packs = pack_bytes > 0;
+            if (!packs || (ws_ok && workspace_bytes >= pack_bytes && ring_pack_pays(trans_a, trans_b, M, N, K, k))) {
+                if (r.splits > 1 && (!ws_ok || workspace_bytes < pack_bytes + gemm_ring_ws_bytes(r, M, N)))
+                    r = plan_ring(M, N, K, batch, cus, false);
+                const size_t used = pack_bytes + gemm_ring_ws_bytes(r, M, N);
+                if (used) {
+                    const size_t a_b = (size_t)((trans_a ? (K - 1) * lda + M : (M - 1) * lda + K) * 2);
+                    const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * 2);
+                    const size_t c_b = (size_t)((M - 1) * ldc + N) * dsize(c_type);
+                    if (overlaps(ws, used, A, a_b) || overlaps(ws, used, B, b_b) || overlaps(ws, used, C, c_b))
+                        return fail(ISAM_ERR_INVALID_ARG, "%s: workspace overlaps A, B or C", who);
+                }
+                if (log_enabled())
+                    fprintf(stderr, "[isam] %s M=%lld N=%lld K=%lld ta=%d tb=%d ring kernel: %s tiles, %d K slices%s%s\n", who,
+                            (long long)M, (long long)N, (long long)K, trans_a, trans_b, r.ring == 1 ? "128x128" : "64x64",
+                            r.splits, k.a ? ", packed operands: A" : "", k.b ? (k.a ? " B" : ", packed operands: B") : "");
+                GemmArgs a{};
+                a.A = k.a ? ws : A;
+                a.B = k.b ? ws + k.a_bytes : B;
+                a.C = C;
+                a.partial = reinterpret_cast<float*>(ws ? ws + pack_bytes : nullptr);
+                a.bias = bias;
+                a.M = M;
+                a.N = N;
+                a.K = K;
+                a.lda = k.a ? k.a_cols : lda;
+                a.ldb = k.b ? k.b_cols : ldb;
+                a.ldc = ldc;
+                a.trans_a = trans_a;
+                a.trans_b = trans_b;
+                a.ab_type = ab_type;
+                a.c_type = c_type;
+                a.accumulate = accumulate;
+                a.batch = batch;
+                a.stride_a = stride_a;
+                a.stride_b = stride_b;
+                a.stride_c = stride_c;
+                hipError_t e = hipSuccess;
+                if (packs) {
+                    PackRows pa{}, pb{};
+                    if (k.a) pa = PackRows{static_cast<const uint16_t*>(A), trans_a ? K : M, trans_a ? M : K, lda,
+                                           reinterpret_cast<uint16_t*>(ws), k.a_cols};
+                    if (k.b) pb = PackRows{static_cast<const uint16_t*>(B), trans_b ? N : K, trans_b ? K : N, ldb,
+                                           reinterpret_cast<uint16_t*>(ws + k.a_bytes), k.b_cols};
+                    e = launch_pack_rows(pa, pb, cus, stream);
+                }
+                if (e == hipSuccess) e = launch_gemm_ring(a, r, RingPadded{k.a, k.b}, cus, stream);
+                return e == hipSuccess ? ISAM_OK : hip_fail(e, who);
+            }
         }
     }
     // bf16 A given as [K][M] is also copied (transposed): the direct-to-LDS
@@ -638,6 +797,38 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
+// Workspace of a product's preferred plan, as far as the sizes tell.
+size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type) {
+    const int cus = device_cus();
+    const GemmPlan p = plan_gemm(M, N, K, ab_type, cus);
+    size_t ws = gemm_ws_bytes(p, M, N);
+    // Rows that the sizes alone make unfit for 16-byte copies (a contiguous
+    // dimension off the vector width), and bf16 A given as [K][M]: room to pack
+    // them, and what the packed product then uses.
+    if (ab_type == ISAM_F32) {
+        const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
+        if (k.pays)
+            return std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
+    }
+    const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
+    const bool a_off = (trans_a ? M : K) % E != 0, b_off = (trans_b ? K : N) % E != 0;
+    if (ab_type == ISAM_BF16) {
+        const RingPlan r = plan_ring(M, N, K, 1, cus, true);
+        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, !a_off && !b_off, K % E == 0, cus)) {
+            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, a_off, b_off);
+            if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, k))
+                ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ring_ws_bytes(r, M, N));
+        }
+    }
+    const bool a_mis = a_off || (trans_a && ab_type == ISAM_BF16);
+    if (a_mis || b_off) {
+        const PackPlan k = pack_plan(trans_a, trans_b, M, N, K, ab_type, a_mis, b_off);
+        if (k.pays)
+            ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, k.Kp, ab_type, cus), M, N));
+    }
+    return ws;
+}
+
 }  // namespace
 
 // ---------------------------------------------------------------------------
@@ -662,25 +853,7 @@ size_t isam_gemm_workspace_size(int trans_a, int trans_b, int64_t M, int64_t N, 
     (void)c_type;
     if (M <= 0 || N <= 0 || K <= 0 || !valid_dtype(ab_type)) return 0;
     if ((trans_a != 0 && trans_a != 1) || (trans_b != 0 && trans_b != 1)) return 0;
-    size_t ws = gemm_ws_bytes(plan_gemm(M, N, K, ab_type, device_cus()), M, N);
-    // Rows that the sizes alone make unfit for 16-byte copies (a contiguous
-    // dimension off the vector width), and bf16 A given as [K][M]: room to pack
-    // them, and what the packed product then uses.
-    if (ab_type == ISAM_F32) {
-        const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
-        if (k.pays)
-            return std::max(ws, k.a_bytes + k.b_bytes +
-                                    gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, device_cus()), M, N));
-    }
-    const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
-    const bool a_mis = (trans_a ? M : K) % E != 0 || (trans_a && ab_type == ISAM_BF16),
-               b_mis = (trans_b ? K : N) % E != 0;
-    if (a_mis || b_mis) {
-        const PackPlan k = pack_plan(trans_a, trans_b, M, N, K, ab_type, a_mis, b_mis);
-        if (k.pays)
-            ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, k.Kp, ab_type, device_cus()), M, N));
-    }
-    return ws;
+    return gemm_query(trans_a, trans_b, M, N, K, ab_type);
 }
 
 static bool dw_out_dims(int64_t H, int64_t W, int64_t kh, int64_t kw, int64_t stride, int64_t pad,
@@ -695,8 +868,7 @@ static size_t dwsep_ws(int64_t batch, int64_t Ho, int64_t Wo, int64_t C_in, int6
                        int64_t C_out, int in_type) {
     const int64_t M = batch * Ho * Wo, K = C_in * cm;
     const size_t y = align256((size_t)M * (size_t)K * dsize(in_type));
-    const GemmPlan p = plan_gemm(M, C_out, K, in_type, device_cus());
-    return y + gemm_ws_bytes(p, M, C_out);
+    return y + gemm_query(0, 0, M, C_out, K, in_type);
 }
 
 // Which separable-convolution path runs: 1 = fused bf16 kernel, 2 = fused

@@ -39,7 +39,6 @@ size_t gemm_fixup_ws_bytes(int64_t M, int64_t N) {
     return tiles * (256 * 256 * 4) + tiles * 128;
 }
 
-namespace {
 // Epochs of in-kernel split sums: a random 64-bit start (so a workspace's
 // stale flags cannot match by accident) and then one value per launch.
 uint64_t next_fixup_epoch() {
@@ -49,6 +48,8 @@ uint64_t next_fixup_epoch() {
     }()};
     return next.fetch_add(1, std::memory_order_relaxed);
 }
+
+namespace {
 
 // C = (accumulate ? C : 0) + bias + sum over splits s = 0, 1, ... of P[s].
 __global__ __launch_bounds__(256) void splitk_reduce_kernel(GemmArgs a, int splits) {

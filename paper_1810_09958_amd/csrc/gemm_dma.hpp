@@ -816,7 +816,7 @@ __global__ __launch_bounds__(64 * WM * WN, BM == 128 ? 2 : 1) void gemm_dma_sk_k
                                      reinterpret_cast<int*>(smem)) && ex.ok;
                 ++ex.n;
             }
-            store_acc_tile<MI, NI, WTM, WTN, NW>(a, acc, smem, m0, n0, wm, wn, wid, ln, true, ex);
+            store_acc_tile<MI, NI, WTM, WTN, NW, false>(a, acc, smem, m0, n0, wm, wn, wid, ln, true, ex);
         }
         __syncthreads();  // the next segment's copies overwrite the stages / staging rows
     }

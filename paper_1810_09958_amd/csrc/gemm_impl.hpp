@@ -70,11 +70,34 @@ struct TileLoader {
         }
         return make_uint4(w[0], w[1], w[2], w[3]);
     }
+    // 16 bytes at the elements' own alignment (gfx950 serves unaligned global loads).
+    __device__ __forceinline__ static uint4 load_whole(const void* p, int64_t base_el) {
+        uint4 v;
+        __builtin_memcpy(&v, static_cast<const char*>(p) + base_el * (int64_t)sizeof(T), 16);
+        return v;
+    }
 
-    // r0: first row (M or N index) of the tile; k0: first K index;
+    // p / rs: the operand and its buffer resource; r0: first row (M or N index) of the tile; k0: first K index;
     // rows_total / kend: valid extents; ld: leading dimension in elements.
-    __device__ __forceinline__ void load(__amdgpu_buffer_rsrc_t rs, int tid, int64_t r0, int64_t k0,
+    __device__ __forceinline__ void load(const void* p, __amdgpu_buffer_rsrc_t rs, int tid, int64_t r0, int64_t k0,
                                          int64_t rows_total, int64_t kend, int64_t ld) {
+        // M / N-contiguous rows that are not 16-byte aligned: tiles wholly
+        // inside the operand are loaded 16 bytes at a time all the same, those at
+        // its edges element by element (a workgroup-uniform choice: 8 branches
+        // per block of rows cost more than they save).
+        if constexpr (!VEC && !KC && UNITS % NT == 0) {
+            if (r0 + ROWS <= rows_total && k0 + BK <= kend) {
+#pragma unroll
+                for (int u = 0; u < NU; ++u) {
+                    const int q = tid + u * NT;
+                    constexpr int RB = ROWS / E;
+                    const int64_t at = (k0 + q / RB * E) * ld + r0 + q % RB * E;
+#pragma unroll
+                    for (int i = 0; i < E; ++i) r[u * E + i] = load_whole(p, at + i * ld);
+                }
+                return;
+            }
+        }
 #pragma unroll
         for (int u = 0; u < NU; ++u) {
             const int q = tid + u * NT;
@@ -87,7 +110,9 @@ struct TileLoader {
                     r[u] = buf_load16(rs, ok ? (uint32_t)((row * ld + k) * (int64_t)sizeof(T)) : kOob);
                 } else {
                     int nv = ok ? (int)((kend - k) < E ? (kend - k) : E) : 0;
-                    r[u] = load_elems(rs, row * ld + k, 1, nv);
+                    // rows along K: whole pieces in one load, the row's last one by element
+                    if (nv == E) r[u] = load_whole(p, row * ld + k);
+                    else r[u] = load_elems(rs, row * ld + k, 1, nv);
                 }
             } else {
                 constexpr int RB = ROWS / E;
@@ -206,7 +231,10 @@ struct NoExtra {
 // 4 accumulators before the bias: extra.slab(v, r, c, step) to the groups of
 // tile rows r, r + step, ... at tile columns c..c+3, extra.one(v, r, c) to one
 // group (tile-local coordinates).
-template <int MI, int NI, int WTM, int WTN, int NW, typename Extra = NoExtra>
+// EDGE: slabs that pass an edge of C or whose rows are not 16-byte aligned are
+// stored straight from the accumulators (kernels with registers to spare for
+// the per-element offsets; the large direct-to-LDS kernels would spill).
+template <int MI, int NI, int WTM, int WTN, int NW, bool EDGE = false, typename Extra = NoExtra>
 __device__ __forceinline__ void store_acc_tile(const GemmArgs& a, f32x16_t (&acc)[MI][NI], char* smem, int64_t m0,
                                                int64_t n0, int wm, int wn, int wid, int lane, bool fixup = false,
                                                const Extra& extra = Extra{}) {
@@ -280,7 +308,57 @@ __device__ __forceinline__ void store_acc_tile(const GemmArgs& a, f32x16_t (&acc
             });
         }
     };
+    // Slabs that pass an edge of C, or C rows that are not 16-byte aligned:
+    // straight from the accumulators, a 32-lane half storing 32 consecutive
+    // columns of one row per instruction (one dword or half word per lane; with
+    // four columns per lane the odd-N product 1000x1537x1023 spent 9 us here).
+    // Lanes outside C store at an offset past the buffer's end.
+    const int64_t c_ext = ((a.M - 1) * ldo + a.N) * osz;
+    auto slab_edge = [&](auto i, auto f32_c, auto addc_c) {
+        constexpr bool F32 = decltype(f32_c)::value, ADDC = decltype(addc_c)::value;
+        constexpr int ES = F32 ? 4 : 2;
+        const int64_t r0 = m0 + wm * WTM + decltype(i)::value * 32 + 4 * (lane >> 5);
+        const int left = a.M - r0 > 32 ? 32 : (int)(a.M - r0);  // rows r0 + dr with dr < left are inside
+        const __amdgpu_buffer_rsrc_t rc = make_rsrc(obase, (uint32_t)c_ext);
+        static_for<NI>([&](auto j) {
+            const int64_t col = col0 + decltype(j)::value * 32 + (lane & 31);
+            const bool col_in = col < a.N;
+            const float b = col_in && !split_out && a.bias ? a.bias[col] : 0.0f;
+            const uint32_t base = (uint32_t)((r0 * ldo + col) * ES), pitch = (uint32_t)(ldo * ES);
+            float old[16];
+            if constexpr (ADDC) {
+                static_for<16>([&](auto v) {
+                    constexpr int vv = decltype(v)::value, dr = 8 * (vv >> 2) + (vv & 3);
+                    const uint32_t off = col_in && dr < left ? base + dr * pitch : kOob;
+                    if constexpr (F32) old[vv] = __uint_as_float(buf_load4(rc, off));
+                    else old[vv] = bf16_to_f32(buf_load2(rc, off) & 0xffffu);
+                });
+            }
+            static_for<16>([&](auto v) {
+                constexpr int vv = decltype(v)::value, dr = 8 * (vv >> 2) + (vv & 3);
+                const uint32_t off = col_in && dr < left ? base + dr * pitch : kOob;
+                float x = acc[decltype(i)::value][decltype(j)::value][vv] + b;
+                if constexpr (ADDC) x = old[vv] + x;
+                if constexpr (F32) __builtin_amdgcn_raw_buffer_store_b32((int)__float_as_uint(x), rc, (int)off, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b16((short)f32_to_bf16(x), rc, (int)off, 0, 0);
+            });
+        });
+    };
     static_for<MI>([&](auto i) {
+        if constexpr (EDGE) {
+            if (!(cols_ok && m0 + wm * WTM + i * 32 + 32 <= a.M) && c_ext < (int64_t(1) << 31)) {
+                using T_ = std::true_type;
+                using F_ = std::false_type;
+                if (out_f32) {
+                    if (add_c) slab_edge(i, T_{}, T_{});
+                    else slab_edge(i, T_{}, F_{});
+                } else {
+                    if (add_c) slab_edge(i, F_{}, T_{});
+                    else slab_edge(i, F_{}, F_{});
+                }
+                return;
+            }
+        }
         static_for<NI>([&](auto j) {
             static_for<16>([&](auto v) {
                 constexpr int vv = decltype(v)::value;
@@ -396,8 +474,8 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmArgs a, Til
 
     auto gload = [&](auto& la, auto& lb, int tile) {
         const int64_t k0 = kbeg + (int64_t)tile * BK;
-        la.load(rsA, tid, m0, k0, a.M, kend, a.lda);
-        lb.load(rsB, tid, n0, k0, a.N, kend, a.ldb);
+        la.load(a.A, rsA, tid, m0, k0, a.M, kend, a.lda);
+        lb.load(a.B, rsB, tid, n0, k0, a.N, kend, a.ldb);
     };
     auto lstore = [&](const auto& la, const auto& lb, int stage) {
         la.store(smem + stage * STAGE, tid);
@@ -440,7 +518,7 @@ __global__ __launch_bounds__(64 * WM * WN) void gemm_tile_kernel(GemmArgs a, Til
     // Epilogue: the accumulators go to C (or the split-K partial sums)
     // through a per-wave LDS buffer, one 32-row slab at a time.
     static_assert(WM * WN * 32 * (WTN * 4 + 16) <= 2 * STAGE, "epilogue staging must fit in LDS");
-    store_acc_tile<MI, NI, WTM, WTN, WM * WN>(a, acc, smem, m0, n0, wm, wn, wid, lane);
+    store_acc_tile<MI, NI, WTM, WTN, WM * WN, !VEC>(a, acc, smem, m0, n0, wm, wn, wid, lane);
 }
 
 // Function table for one element type: [tile][trans_a][trans_b][vec].

@@ -67,6 +67,23 @@ struct GemmPlan {
 int gemm_sk_grid(int tile, int cus);
 size_t gemm_sk_ws_bytes(int tile, int grid);
 bool gemm_sk_tile(int tile);
+// Mid-size bf16 products (gemm_ring.hpp), any operand layout with 16-byte
+// aligned rows: instance (0: none, 1: 128x128 tiles, 2: 64x64 tiles) and K
+// slices per tile, summed in the kernel through the workspace (a.partial).
+struct RingPlan {
+    int ring, splits;
+};
+// Rows are readable to ld values each (operands packed by the library): the
+// last row's 16-byte pieces may then pass the row's last value.
+struct RingPadded {
+    bool a, b;
+};
+void gemm_ring_dims(int ring, int* bm, int* bn);
+size_t gemm_ring_ws_bytes(const RingPlan& r, int64_t M, int64_t N);
+hipError_t launch_gemm_ring(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int cus, hipStream_t s);
+// One value per launch for flags that stale workspace contents must not match
+// (random 64-bit start).
+uint64_t next_fixup_epoch();
 // Small products: at most kSmallMaxTiles output tiles of 32x32 and K <= kSmallMaxK
 // (A K-contiguous, 16-byte aligned operands, batch 1: checked by the caller).
 constexpr int64_t kSmallMaxTiles = 64;
@@ -108,6 +125,16 @@ hipError_t launch_split6(const float* src, int64_t s_rows, int64_t s_cols, int64
                          hipStream_t s);
 hipError_t launch_pack(const void* src, int64_t s_rows, int64_t s_cols, int64_t ld, void* dst, int64_t d_rows,
                        int64_t d_cols, int esize, bool transpose, int cus, hipStream_t s);
+
+// bf16 rows src[rows][s_cols] (leading dimension ld) into dense 16-byte aligned
+// rows dst[rows][d_cols], zeros past s_cols (d_cols a multiple of 8); rows = 0: nothing.
+struct PackRows {
+    const uint16_t* src;
+    int64_t rows, s_cols, ld;
+    uint16_t* dst;
+    int64_t d_cols;
+};
+hipError_t launch_pack_rows(const PackRows& a, const PackRows& b, int cus, hipStream_t s);
 
 // Depthwise kh x kw convolution, NHWC.  Y is [batch][Ho][Wo][C*cm] in y_type.
 struct DwArgs {

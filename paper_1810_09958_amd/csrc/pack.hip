@@ -68,6 +68,33 @@ __global__ __launch_bounds__(kPackThreads) void pack_copy_kernel(const T* __rest
     }
 }
 
+// Rows of one or two bf16 matrices into dense rows of d_cols values (a
+// multiple of 8), zeros past s_cols: one launch for both operands of a
+// mid-size product, whose copies are too short to fill the device one after
+// the other.  A 16-byte group inside its row is one load at the row's own
+// alignment (gfx950 serves unaligned global loads).
+__global__ __launch_bounds__(kPackThreads) void pack_rows_kernel(PackRows a, PackRows b) {
+    const uint32_t ua = (uint32_t)a.rows * (uint32_t)(a.d_cols / 8), ub = (uint32_t)b.rows * (uint32_t)(b.d_cols / 8);
+    for (uint32_t u = blockIdx.x * kPackThreads + threadIdx.x; u < ua + ub; u += gridDim.x * kPackThreads) {
+        const bool second = u >= ua;
+        const PackRows& o = second ? b : a;
+        const uint32_t v = second ? u - ua : u, upr = (uint32_t)(o.d_cols / 8);
+        const uint32_t i = v / upr;
+        const int64_t j0 = (int64_t)(v - i * upr) * 8;
+        const uint16_t* q = o.src + (int64_t)i * o.ld + j0;
+        uint4 w;
+        if (j0 + 8 <= o.s_cols) {
+            __builtin_memcpy(&w, q, 16);
+        } else {
+            uint32_t h[8];
+#pragma unroll
+            for (int k = 0; k < 8; ++k) h[k] = j0 + k < o.s_cols ? q[k] : 0u;
+            w = make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+        }
+        *reinterpret_cast<uint4*>(o.dst + (int64_t)i * o.d_cols + j0) = w;
+    }
+}
+
 // bf16 transpose with 16-byte source rows: dst[i][j] = src[j][i] (j < s_rows,
 // i < s_cols), else 0.  A lane reads an 8x8 block (8 source rows, 16 bytes
 // each), transposes it in registers and writes 8 destination rows of 16 bytes;
@@ -211,6 +238,14 @@ hipError_t launch_pack(const void* src, int64_t s_rows, int64_t s_cols, int64_t 
             else go(pack_copy_kernel<uint32_t, 4>, s32, d32);
         }
     }
+    return hipGetLastError();
+}
+
+hipError_t launch_pack_rows(const PackRows& a, const PackRows& b, int cus, hipStream_t s) {
+    const int64_t units = a.rows * (a.d_cols / 8) + b.rows * (b.d_cols / 8);
+    if (units <= 0) return hipSuccess;
+    const int64_t blocks = std::min<int64_t>((units + kPackThreads - 1) / kPackThreads, (int64_t)cus * 16);
+    hipLaunchKernelGGL(pack_rows_kernel, dim3((unsigned)blocks), dim3(kPackThreads), 0, s, a, b);
     return hipGetLastError();
 }
 
