@@ -388,22 +388,31 @@ PackPlan pack_plan(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, in
 
 // Large fp32 products run on the bf16 matrix cores: each operand value is
 // split into three bf16 terms (pack.hip) laid out as six K blocks, A as
-// (h, h, m, h, l, m) and B as (h, m, h, l, h, m), so that one bf16 product over
-// K' = 6 Kp forms hh + hm + mh + hl + lh + mm -- the fp32 product to within
-// the dropped terms' 2^-23 relative size, accumulated in fp32.  Six bf16
+// (m, l, h, m, h, h) and B as (m, h, l, h, m, h), so that one bf16 product over
+// K' = 6 Kp forms mm + lh + hl + mh + hm + hh -- the fp32 product to within
+// the dropped terms' 2^-23 relative size, accumulated in fp32, the small products
+// first (a sum that already holds hh would round each of them at full size:
+// 2048x1024x1024 in two K slices 4.5e-7 of the result's norm).  Six bf16
 // products cost less than a quarter of one fp32 product on the matrix cores
 // (fp32 8192^3: 8.47 ms on the fp32 tile kernel).  Needs A [M][K] (no
 // transpose), B [N][K] or [K][N] with N a multiple of 8, and workspace for
 // the split copies (12 bytes per operand value); only products where the
 // copies cost well under the time saved (M N >= 512 (M + N), large tiles).
-constexpr uint32_t kSplitPatA = 0u | 0u << 2 | 1u << 4 | 0u << 6 | 2u << 8 | 1u << 10;
-constexpr uint32_t kSplitPatB = 0u | 1u << 2 | 0u << 4 | 2u << 6 | 0u << 8 | 1u << 10;
+constexpr uint32_t kSplitPatA = 1u | 2u << 2 | 0u << 4 | 1u << 6 | 0u << 8 | 0u << 10;
+constexpr uint32_t kSplitPatB = 1u | 0u << 2 | 2u << 4 | 0u << 6 | 1u << 8 | 0u << 10;
 
 struct SplitPlan {
     bool pays = false;
     int64_t Kp = 0;                   // K of each block
     size_t a_bytes = 0, b_bytes = 0;  // each a multiple of 256
 };
+
+// fp32 grids below one 128x128 tile per CU: the kernel that forms the terms in
+// registers (gemm_f32x.hpp) with K slices, instead of split copies.
+bool f32x_grid(int64_t M, int64_t N, int cus) {
+    const char* env = getenv("ISAM_GEMM_CONFIG");
+    return cdiv(M, 128) * cdiv(N, 128) < cus && !(env && strstr(env, "f32x=0"));
+}
 
 SplitPlan split_plan(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K) {
     SplitPlan k;
@@ -431,6 +440,23 @@ bool pack_b_needed(int trans_b, int64_t N, int64_t K, int ab_type, const void* B
     return ((uintptr_t)B & 15) || (ldb * es) % 16 || (trans_b ? K : N) % E;
 }
 
+// Cost of the fp32 kernel on bf16 terms (gemm_f32x.hpp), us, and of the kernels
+// it stands beside, fitted to a sweep on MI355X.  A workgroup holds its CU
+// alone: per round of workgroups the start and end of one and its 64-deep K
+// tiles (128x128 / 64x64 / 128x64 at 2.9 / 0.78 / 1.45 us with the whole chip
+// busy, which power limits: 1.1 PFLOP/s of bf16 products).
+double f32x_us(int ring, int64_t iters, int64_t per_cu, int64_t sp) {
+    static const double fixed[3] = {8.5, 6.8, 8.0}, rate[3] = {2.9, 0.78, 1.45};
+    const double split = sp <= 1 ? 0.0 : ring == 2 ? 0.7 + 1.6 * (double)sp : 2.5 + 1.1 * (double)sp;
+    return (double)per_cu * (fixed[ring - 1] + rate[ring - 1] * (double)iters) + split;
+}
+// The fp32 tile kernel runs at about 95 TFLOP/s, element by element at about 40
+// (the term kernel then also copies the operands, 4 us).
+bool f32x_pays(double us, int64_t M, int64_t N, int64_t K, int64_t batch, bool aligned) {
+    const double flops = 2.0 * (double)batch * (double)M * (double)N * (double)K;
+    return us + (aligned ? 0.0 : 4.0) < 0.93 * (6.0 + flops / (aligned ? 95e6 : 40e6));
+}
+
 // bf16 products whose 128x128 tiles leave CUs idle run on the LDS-ring kernel
 // (gemm_ring.hpp), any layout.  Tile and K split by a cost model of that
 // kernel, fitted to a sweep on MI355X: a 64-deep K tile takes 0.47 us for a
@@ -444,22 +470,27 @@ bool pack_b_needed(int trans_b, int64_t N, int64_t K, int ab_type, const void* B
 //   648x1520x3096 NT 20 / 28, 4968x128x2064 NN 12.3 / 22.5, 512x512x4096 NN 11.9 / 21.9.
 // ISAM_GEMM_CONFIG ring=0 switches it off, ring=1 / ring=2 force 128x128 / 64x64
 // tiles and rs=<n> the K slices; settings of the other kernels also switch it off.
-RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool may_split) {
+//
+// fp32 products take the same tiles and K slices on the kernel of gemm_f32x.hpp
+// (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size.
+RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus, bool may_split) {
     RingPlan none{0, 1};
     if (M <= 0 || N <= 0 || K <= 0) return none;
+    const bool f32 = ab_type == kF32;
     const int64_t nk = cdiv(K, 64);
     int force = 0, force_s = 0;
     if (const char* env = getenv("ISAM_GEMM_CONFIG")) {
         for (const char* k : {"tile=", "splits=", "dma=", "dmaw=", "sk=1", "stream=1", "ring=0"})
-            if (strstr(env, k)) return none;
+            if (strstr(env, k) && !(f32 && !strcmp(k, "ring=0"))) return none;
+        if (f32 && strstr(env, "f32x=0")) return none;
         const char* q;
-        if ((q = strstr(env, "ring="))) force = std::min(2, atoi(q + 5));
+        if ((q = strstr(env, f32 ? "f32x=" : "ring="))) force = std::min(f32 ? 3 : 2, atoi(q + 5));
         if ((q = strstr(env, "rs="))) force_s = atoi(q + 3);
     }
-    if (!force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
+    if (!f32 && !force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
     RingPlan best = none;
     double best_us = 0;
-    for (int ring = 1; ring <= 2; ++ring) {
+    for (int ring = 1; ring <= (f32 ? 3 : 2); ++ring) {
         if (force && ring != force) continue;
         int bm, bn;
         gemm_ring_dims(ring, &bm, &bn);
@@ -468,7 +499,7 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool
         for (int64_t sp = 1; sp <= most; ++sp) {
             if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
             const int64_t iters = cdiv(nk, sp), per_cu = cdiv(tiles * cdiv(nk, iters), cus);
-            const double us = ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
+            const double us = f32 ? f32x_us(ring, iters, per_cu, sp) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
                                         : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
                                               (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);
             if (!best.ring || us < best_us) {
@@ -477,33 +508,35 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int64_t batch, int cus, bool
             }
         }
     }
+    if (f32 && !force && !f32x_pays(best_us, M, N, K, batch, aligned)) return none;
     return best;
 }
 
 // Operand copies (pack.hip) that let a product with unaligned rows take the
 // ring kernel: each operand that needs it copied row by row into rows
-// of a multiple of 8 values (zeros past the row's end: K positions beyond K
+// of a multiple of 16 bytes (zeros past the row's end: K positions beyond K
 // add exact zeros, columns beyond M or N are not stored).
 struct RingPack {
     bool a = false, b = false;
     int64_t a_cols = 0, b_cols = 0;   // packed row lengths
     size_t a_bytes = 0, b_bytes = 0;  // each a multiple of 256
 };
-RingPack ring_pack(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a, bool need_b) {
+RingPack ring_pack(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, bool need_a, bool need_b) {
     RingPack k;
+    const int64_t es = (int64_t)dsize(ab_type), line = 128 / es, unit = 16 / es;
     auto al = [](int64_t v) { return (size_t)((v + 255) & ~(int64_t)255); };
     // whole 128-byte lines where that adds at most an eighth: a copied row
     // segment that straddles lines costs the copies up to half of their rate
-    auto cols = [](int64_t v) { return (cdiv(v, 64) * 64 - v) * 8 <= v ? cdiv(v, 64) * 64 : cdiv(v, 8) * 8; };
+    auto cols = [=](int64_t v) { return (cdiv(v, line) * line - v) * 8 <= v ? cdiv(v, line) * line : cdiv(v, unit) * unit; };
     k.a = need_a;
     k.b = need_b;
     if (need_a) {
         k.a_cols = cols(trans_a ? M : K);
-        k.a_bytes = al((trans_a ? K : M) * k.a_cols * 2);
+        k.a_bytes = al((trans_a ? K : M) * k.a_cols * es);
     }
     if (need_b) {
         k.b_cols = cols(trans_b ? K : N);
-        k.b_bytes = al((trans_b ? N : K) * k.b_cols * 2);
+        k.b_bytes = al((trans_b ? N : K) * k.b_cols * es);
     }
     return k;
 }
@@ -513,21 +546,23 @@ RingPack ring_pack(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bo
 // 326x468x1573 NN 26 against 13, but 298x1281x100 NN 8.8 against 10 and, with
 // both operands' rows along K (NT), 300^3 7.3 against 10, 2021x271x374 7.7 against
 // 10.2, 700x700x701 12.3 against 10.9.
-bool ring_pack_pays(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, const RingPack& k) {
+bool ring_pack_pays(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, int cus, const RingPack& k) {
     const char* env = getenv("ISAM_GEMM_CONFIG");
     if (env && strstr(env, "pack=0")) return false;
+    // fp32 grids that fill the chip are packed by pack_plan (whole K tiles)
+    if (ab_type == kF32 && !f32x_grid(M, N, cus)) return false;
     const bool pays = trans_a || !trans_b ? K > 128 && M * N * K >= (int64_t(1) << 20) : M * N * K >= (int64_t(1) << 28);
     return pays && (int64_t)k.a_bytes <= kMaxExtent && (int64_t)k.b_bytes <= kMaxExtent;
 }
 
 // Whether a plan of plan_gemm keeps its special kernel (skinny, narrow, small or
 // streaming) for these operands instead of the ring kernel.
-bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool vec,
+bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, bool vec,
                     bool a_rows_aligned, int cus) {
     if (p.skinny == 4) return !trans_a && !trans_b && a_rows_aligned;
     if (p.skinny) return vec && !trans_a && !trans_b;
     if (p.small) return vec && !trans_a;
-    return vec && !trans_a && !trans_b && K <= kStreamMaxK && N <= 256 && N % 4 == 0 && cdiv(M, 32) >= cus;
+    return ab_type == kBF16 && vec && !trans_a && !trans_b && K <= kStreamMaxK && N <= 256 && N % 4 == 0 && cdiv(M, 32) >= cus;
 }
 
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
@@ -585,7 +620,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         char* ws = static_cast<char*>(workspace);
         const size_t split_bytes = k.a_bytes + k.b_bytes;
-        if (k.pays && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes) {
+        if (k.pays && !f32x_grid(M, N, device_cus()) && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes) {
             const int64_t es = (int64_t)dsize(ab_type);
             const size_t a_b = (size_t)(((M - 1) * lda + K) * es);
             const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
@@ -610,30 +645,33 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                             c_type, C, ldc, bias, ws + split_bytes, workspace_bytes - split_bytes, stream, who);
         }
     }
-    if (ab_type == kBF16 && K > 0) {
+    if (K > 0) {
         const int cus = device_cus();
+        const int64_t es = (int64_t)dsize(ab_type);
         const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
-        RingPlan r = plan_ring(M, N, K, batch, cus, batch == 1);
-        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, p.vec && batch == 1, !((uintptr_t)A & 15) && lda % 8 == 0, cus)) {
-            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, need_a, need_b);
+        RingPlan r = plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
+        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
+                                      !((uintptr_t)A & 15) && lda * es % 16 == 0, cus)) {
+            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, need_a, need_b);
             const size_t pack_bytes = k.a_bytes + k.b_bytes;
             char* ws = static_cast<char*>(workspace);
             const bool ws_ok = ws && ((uintptr_t)ws & 255) == 0 && batch == 1;
             const bool packs = pack_bytes > 0;
-            if (!packs || (ws_ok && workspace_bytes >= pack_bytes && ring_pack_pays(trans_a, trans_b, M, N, K, k))) {
-                if (r.splits > 1 && (!ws_ok || workspace_bytes < pack_bytes + gemm_ring_ws_bytes(r, M, N)))
-                    r = plan_ring(M, N, K, batch, cus, false);
+            const bool fits = !packs || (ws_ok && workspace_bytes >= pack_bytes && ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k));
+            if (fits && r.splits > 1 && (!ws_ok || workspace_bytes < pack_bytes + gemm_ring_ws_bytes(r, M, N)))
+                r = plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, false);
+            if (fits && r.ring) {
                 const size_t used = pack_bytes + gemm_ring_ws_bytes(r, M, N);
                 if (used) {
-                    const size_t a_b = (size_t)((trans_a ? (K - 1) * lda + M : (M - 1) * lda + K) * 2);
-                    const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * 2);
+                    const size_t a_b = (size_t)((trans_a ? (K - 1) * lda + M : (M - 1) * lda + K) * es);
+                    const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
                     const size_t c_b = (size_t)((M - 1) * ldc + N) * dsize(c_type);
                     if (overlaps(ws, used, A, a_b) || overlaps(ws, used, B, b_b) || overlaps(ws, used, C, c_b))
                         return fail(ISAM_ERR_INVALID_ARG, "%s: workspace overlaps A, B or C", who);
                 }
                 if (log_enabled())
-                    fprintf(stderr, "[isam] %s M=%lld N=%lld K=%lld ta=%d tb=%d ring kernel: %s tiles, %d K slices%s%s\n", who,
-                            (long long)M, (long long)N, (long long)K, trans_a, trans_b, r.ring == 1 ? "128x128" : "64x64",
+                    fprintf(stderr, "[isam] %s M=%lld N=%lld K=%lld ta=%d tb=%d ab=%d ring kernel: %s tiles, %d K slices%s%s\n", who,
+                            (long long)M, (long long)N, (long long)K, trans_a, trans_b, ab_type, r.ring == 1 ? "128x128" : r.ring == 2 ? "64x64" : "128x64",
                             r.splits, k.a ? ", packed operands: A" : "", k.b ? (k.a ? " B" : ", packed operands: B") : "");
                 GemmArgs a{};
                 a.A = k.a ? ws : A;
@@ -658,14 +696,17 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                 a.stride_c = stride_c;
                 hipError_t e = hipSuccess;
                 if (packs) {
-                    PackRows pa{}, pb{};
-                    if (k.a) pa = PackRows{static_cast<const uint16_t*>(A), trans_a ? K : M, trans_a ? M : K, lda,
-                                           reinterpret_cast<uint16_t*>(ws), k.a_cols};
-                    if (k.b) pb = PackRows{static_cast<const uint16_t*>(B), trans_b ? N : K, trans_b ? K : N, ldb,
-                                           reinterpret_cast<uint16_t*>(ws + k.a_bytes), k.b_cols};
+                    PackRows pa{}, pb{};  // in 2-byte words
+                    const int64_t w = es / 2;
+                    if (k.a) pa = PackRows{static_cast<const uint16_t*>(A), trans_a ? K : M, (trans_a ? M : K) * w, lda * w,
+                                           reinterpret_cast<uint16_t*>(ws), k.a_cols * w};
+                    if (k.b) pb = PackRows{static_cast<const uint16_t*>(B), trans_b ? N : K, (trans_b ? K : N) * w, ldb * w,
+                                           reinterpret_cast<uint16_t*>(ws + k.a_bytes), k.b_cols * w};
                     e = launch_pack_rows(pa, pb, cus, stream);
                 }
-                if (e == hipSuccess) e = launch_gemm_ring(a, r, RingPadded{k.a, k.b}, cus, stream);
+                if (e == hipSuccess)
+                    e = ab_type == kF32 ? launch_gemm_f32x(a, r, RingPadded{k.a, k.b}, cus, stream)
+                                        : launch_gemm_ring(a, r, RingPadded{k.a, k.b}, cus, stream);
                 return e == hipSuccess ? ISAM_OK : hip_fail(e, who);
             }
         }
@@ -807,16 +848,16 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
     // them, and what the packed product then uses.
     if (ab_type == ISAM_F32) {
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
-        if (k.pays)
+        if (k.pays && !f32x_grid(M, N, cus))
             return std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
     }
     const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
     const bool a_off = (trans_a ? M : K) % E != 0, b_off = (trans_b ? K : N) % E != 0;
-    if (ab_type == ISAM_BF16) {
-        const RingPlan r = plan_ring(M, N, K, 1, cus, true);
-        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, !a_off && !b_off, K % E == 0, cus)) {
-            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, a_off, b_off);
-            if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, k))
+    {
+        const RingPlan r = plan_ring(M, N, K, ab_type, !a_off && !b_off, 1, cus, true);
+        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, !a_off && !b_off, K % E == 0, cus)) {
+            const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, a_off, b_off);
+            if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k))
                 ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ring_ws_bytes(r, M, N));
         }
     }

@@ -13,7 +13,10 @@ GemmRingFn ring_fn(int ta, int tb) {
 
 }  // namespace
 
-void gemm_ring_dims(int ring, int* bm, int* bn) { *bm = *bn = ring == 1 ? 128 : 64; }
+void gemm_ring_dims(int ring, int* bm, int* bn) {
+    *bm = ring == 2 ? 64 : 128;
+    *bn = ring == 1 ? 128 : 64;
+}
 
 size_t gemm_ring_ws_bytes(const RingPlan& r, int64_t M, int64_t N) {
     if (!r.ring || r.splits <= 1) return 0;
@@ -23,13 +26,8 @@ size_t gemm_ring_ws_bytes(const RingPlan& r, int64_t M, int64_t N) {
     return tiles * ((size_t)r.splits * bm * bn * 4 + 64);
 }
 
-hipError_t launch_gemm_ring(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int cus, hipStream_t s) {
-    if (a.ab_type != kBF16 || (r.ring != 1 && r.ring != 2) || a.K <= 0) return hipErrorInvalidValue;
-    // 128x128: 8 waves of 64x32, four stages (128 KB), one workgroup per CU;
-    // 64x64: 4 waves of 32x32, four stages (64 KB), two workgroups per CU.
-    const int threads = r.ring == 1 ? 512 : 256;
-    const GemmRingFn fn = r.ring == 1 ? ring_fn<128, 128, 2, 4, 4, 2>(a.trans_a, a.trans_b)
-                                      : ring_fn<64, 64, 2, 2, 4, 2>(a.trans_a, a.trans_b);
+// What a launch of either ring kernel (es: bytes per operand value) passes besides the operands.
+hipError_t ring_args(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int es, int cus, RingArgs* out) {
     int bm, bn;
     gemm_ring_dims(r.ring, &bm, &bn);
     RingArgs t{};
@@ -46,11 +44,25 @@ hipError_t launch_gemm_ring(const GemmArgs& a, const RingPlan& r, const RingPadd
     if (t.splits > 255 || (t.splits > 1 && ((uintptr_t)a.partial & 255))) return hipErrorInvalidValue;
     const int64_t a_rows = a.trans_a ? a.K : a.M, a_cols = a.trans_a ? a.M : a.K;
     const int64_t b_rows = a.trans_b ? a.N : a.K, b_cols = a.trans_b ? a.K : a.N;
-    t.a_bytes = (uint32_t)((pad.a ? a_rows * a.lda : (a_rows - 1) * a.lda + a_cols) * 2);
-    t.b_bytes = (uint32_t)((pad.b ? b_rows * a.ldb : (b_rows - 1) * a.ldb + b_cols) * 2);
+    t.a_bytes = (uint32_t)((pad.a ? a_rows * a.lda : (a_rows - 1) * a.lda + a_cols) * es);
+    t.b_bytes = (uint32_t)((pad.b ? b_rows * a.ldb : (b_rows - 1) * a.ldb + b_cols) * es);
     t.epoch = next_fixup_epoch() & ((1ull << 40) - 1);
     if (!t.epoch) t.epoch = 1;
     t.arrive = reinterpret_cast<uint64_t*>(reinterpret_cast<char*>(a.partial) + (size_t)tiles * t.splits * bm * bn * 4);
+    *out = t;
+    return hipSuccess;
+}
+
+hipError_t launch_gemm_ring(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int cus, hipStream_t s) {
+    if (a.ab_type != kBF16 || (r.ring != 1 && r.ring != 2) || a.K <= 0) return hipErrorInvalidValue;
+    // 128x128: 8 waves of 64x32, four stages (128 KB), one workgroup per CU;
+    // 64x64: 4 waves of 32x32, four stages (64 KB), two workgroups per CU.
+    const int threads = r.ring == 1 ? 512 : 256;
+    const GemmRingFn fn = r.ring == 1 ? ring_fn<128, 128, 2, 4, 4, 2>(a.trans_a, a.trans_b)
+                                      : ring_fn<64, 64, 2, 2, 4, 2>(a.trans_a, a.trans_b);
+    RingArgs t{};
+    hipError_t e = ring_args(a, r, pad, 2, cus, &t);
+    if (e != hipSuccess) return e;
     const dim3 grid((unsigned)(t.xcds * t.per_xcd * t.splits), 1, (unsigned)(a.batch > 1 ? a.batch : 1));
     hipLaunchKernelGGL(fn, grid, dim3(threads), 0, s, a, t);
     return hipGetLastError();

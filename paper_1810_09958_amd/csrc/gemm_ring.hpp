@@ -290,4 +290,6 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmArgs a
 
 typedef void (*GemmRingFn)(GemmArgs, RingArgs);
 
+hipError_t ring_args(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int es, int cus, RingArgs* out);
+
 }  // namespace isam

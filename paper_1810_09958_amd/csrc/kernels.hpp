@@ -68,7 +68,7 @@ int gemm_sk_grid(int tile, int cus);
 size_t gemm_sk_ws_bytes(int tile, int grid);
 bool gemm_sk_tile(int tile);
 // Mid-size bf16 products (gemm_ring.hpp), any operand layout with 16-byte
-// aligned rows: instance (0: none, 1: 128x128 tiles, 2: 64x64 tiles) and K
+// aligned rows: instance (0: none, 1: 128x128 tiles, 2: 64x64 tiles, 3: 128x64 tiles, fp32 only) and K
 // slices per tile, summed in the kernel through the workspace (a.partial).
 struct RingPlan {
     int ring, splits;
@@ -81,6 +81,9 @@ struct RingPadded {
 void gemm_ring_dims(int ring, int* bm, int* bn);
 size_t gemm_ring_ws_bytes(const RingPlan& r, int64_t M, int64_t N);
 hipError_t launch_gemm_ring(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int cus, hipStream_t s);
+// fp32 products on bf16 terms formed in registers (gemm_f32x.hpp): the same
+// tiles, K slices and workspace.
+hipError_t launch_gemm_f32x(const GemmArgs& a, const RingPlan& r, const RingPadded& pad, int cus, hipStream_t s);
 // One value per launch for flags that stale workspace contents must not match
 // (random 64-bit start).
 uint64_t next_fixup_epoch();

@@ -1,0 +1,103 @@
+"""fp32 products on bf16 terms formed in registers: against 64-bit products, also out of the terms' range."""
+import math
+
+import pytest
+import torch
+
+pytestmark = pytest.mark.gpu
+
+import paper_1810_09958_amd as isam
+
+
+def _tol(K):
+    # Of sum |a||b|: the dropped terms (below 2^-23), the 32-bit sums (one rounding per 16 values
+    # of K, the five small products' far below, at most 24 when the K steps and slices are added)
+    # and the result's.
+    return 2.0 ** -23 + (K / 16 + 26) * 2.0 ** -24
+
+
+def _operands(M, N, K, ta, tb, pad, seed):
+    g = torch.Generator(device="cuda")
+    g.manual_seed(seed)
+
+    def make(r, c):
+        w = torch.full((r, c + pad), float("nan"), device="cuda")
+        w[:, :c] = torch.randn((r, c), generator=g, device="cuda")
+        return w[:, :c]
+
+    return make(K, M) if ta else make(M, K), make(N, K) if tb else make(K, N)
+
+
+def _check(A, B, ta, tb, acc=False, ct=torch.float32, workspace=None):
+    A64, B64 = (A.t() if ta else A).double().contiguous(), (B.t() if tb else B).double().contiguous()
+    K = A64.shape[1]
+    C = torch.randn((A64.shape[0], B64.shape[1]), device="cuda").to(ct)
+    ref = A64 @ B64 + (C.double() if acc else 0)
+    S = A64.abs() @ B64.abs() + (C.double().abs() if acc else 0)
+    isam.gemm(A, B, C, trans_a=bool(ta), trans_b=bool(tb), accumulate=acc, workspace=workspace)
+    tol = _tol(K) + (2.0 ** -8 if ct == torch.bfloat16 else 0)
+    fin = S < 3e38  # the others overflow or hold an infinity or a NaN: the same value in both
+    assert bool(((C.double() - ref).abs()[fin] <= tol * S[fin] + K * 2.0 ** -126).all())  # products below 2^-126 may be flushed
+    want = ref.float()[~fin]
+    same = (C.float()[~fin] == want) | (torch.isnan(want) & torch.isnan(C.float()[~fin]))
+    assert bool(same.all())
+    return C
+
+
+# Edges of the tiles, K of one tile and less, ragged K tiles, more slices than K tiles.
+@pytest.mark.parametrize("ring", [1, 2, 3])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,rs", [(4, 4, 4, 1), (128, 64, 64, 2), (132, 68, 36, 1), (64, 260, 640, 4),
+                                      (260, 132, 652, 5), (128, 128, 2048, 16), (388, 520, 200, 3)])
+def test_f32x_forced(ring, ta, tb, M, N, K, rs, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs={rs},skinny=0,small=0")
+    _check(*_operands(M, N, K, ta, tb, 0, M + K), ta, tb)
+    _check(*_operands(M, N, K, ta, tb, 4, N + K), ta, tb, acc=True, ct=torch.bfloat16)
+
+
+# As planned: aligned and odd sizes (operands copied into padded rows), with too little
+# workspace for slices or copies, and the strided batch of a convolution.
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(1024, 512, 2048), (999, 1001, 1003), (2052, 516, 516)])
+def test_f32x_planned(ta, tb, M, N, K, monkeypatch):
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    A, B = _operands(M, N, K, ta, tb, 0, M)
+    _check(A, B, ta, tb)
+    _check(A, B, ta, tb, workspace=torch.empty(256, device="cuda", dtype=torch.uint8))
+    x, w = torch.randn((3, 700, 256), device="cuda"), torch.randn((5, 256, 384), device="cuda") / 36
+    y = isam.conv1d(x, w).double()
+    ref = sum(x.double()[:, d:d + 696].reshape(-1, 256).contiguous() @ w[d].double() for d in range(5))
+    S = sum(x.double().abs()[:, d:d + 696].reshape(-1, 256).contiguous() @ w[d].double().abs() for d in range(5))
+    assert bool(((y.reshape(-1, 384) - ref).abs() <= _tol(5 * 256) * S).all())
+
+
+# Values that do not split into bf16 terms: infinities, NaNs, magnitudes from 2^60 and rows below
+# 2^-90.  The workgroups that read them form their tiles in fp32.
+@pytest.mark.parametrize("ring,rs", [(1, 1), (1, 3), (2, 1), (2, 4), (3, 2)])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_f32x_range(ring, rs, ta, tb, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs={rs},skinny=0,small=0")
+    A, B = _operands(260, 200, 328, ta, tb, 0, 9)
+    Am, Bm = (A.t() if ta else A), (B.t() if tb else B)
+    Am[3] *= 2.0 ** 100
+    Am[7] *= 2.0 ** -100
+    Am[130, 200] = math.inf
+    Am[131, 327] = -math.inf
+    Am[200, 5] = math.nan
+    Bm[:, 150] *= 2.0 ** -110
+    Bm[17, 2] = 1e37
+    C = _check(A, B, ta, tb)
+    assert bool(torch.isinf(C[130]).any()) and bool(torch.isnan(C[200]).all())
+
+
+def test_f32x_error_is_below_the_fp32_instructions(monkeypatch):
+    # Against 64 bits, over the products that moved from the fp32 tile kernel: no larger.
+    for M, N, K, tb in [(2048, 1024, 1024, 1), (512, 512, 4096, 0), (8192, 256, 256, 0)]:
+        A, B = _operands(M, N, K, 0, tb, 0, K)
+        ref = A.double() @ (B.t() if tb else B).double().contiguous()
+        err = {}
+        for env in ("", "f32x=0,f32split=0"):
+            monkeypatch.setenv("ISAM_GEMM_CONFIG", env)
+            C = isam.gemm(A, B, trans_b=bool(tb))
+            err[env] = float((C.double() - ref).norm() / ref.norm())
+        assert err[""] <= err["f32x=0,f32split=0"], err
