@@ -42,6 +42,26 @@ def test_generic_path(dt, cm, k, stride, pad):
     _case(2, 10, 9, 8, 12, cm=cm, k=k, stride=stride, pad=pad, dt=dt)
 
 
+# Window kernel (3x3 stride 2, 5x5, whole channel vectors): last row pair and column short, one
+# row or column of output, padding from none to beyond the window, images smaller than the window.
+@pytest.mark.parametrize("dt,ot", [("f32", "f32"), ("bf16", "bf16")])
+@pytest.mark.parametrize("b,H,W,C,k,stride,pad", [(2, 15, 17, 24, 3, 2, 1), (1, 2, 3, 8, 3, 2, 1), (3, 8, 3, 264, 3, 2, 0),
+                                                  (1, 5, 6, 40, 3, 2, 3), (9, 31, 33, 64, 5, 1, 2), (12, 41, 47, 64, 5, 2, 2),
+                                                  (9, 30, 29, 64, 5, 1, 0), (40, 3, 60, 64, 5, 1, 4), (4, 3, 4, 16, 5, 2, 2)])
+def test_window_kernel(dt, ot, b, H, W, C, k, stride, pad):
+    _case(b, H, W, C, 12, k=k, stride=stride, pad=pad, dt=dt, ot=ot, seed=H)
+
+
+def test_window_kernel_skips_taps_outside_the_image():
+    # an infinite tap counts only where its input lies inside the image
+    for k, stride in ((3, 2), (5, 1)):
+        x, D, P = torch.randn(9, 32, 32, 64, device="cuda"), torch.randn(k, k, 64, 1, device="cuda"), torch.randn(64, 8, device="cuda")
+        D[0, 0, 5] = float("inf")
+        y = isam.dwsep_conv(x, D, P, stride=stride, pad=k // 2)
+        assert bool(torch.isfinite(y[:, 0]).all()) and bool(torch.isfinite(y[:, :, 0]).all())
+        assert not bool(torch.isfinite(y[:, -1, -1]).any())
+
+
 @pytest.mark.parametrize("dt", ["f32", "bf16"])
 def test_channels_not_vector_multiple(dt):
     _case(2, 7, 7, 5, 9, dt=dt)
