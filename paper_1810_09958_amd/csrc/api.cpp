@@ -487,6 +487,7 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, i
         if ((q = strstr(env, f32 ? "f32x=" : "ring="))) force = std::min(f32 ? 3 : 2, atoi(q + 5));
         if ((q = strstr(env, "rs="))) force_s = atoi(q + 3);
     }
+    if (f32 && !force && !f32x_pays(f32x_us(2, 1, 1, 1), M, N, K, batch, aligned)) return none;  // not even at its least
     if (!f32 && !force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
     RingPlan best = none;
     double best_us = 0;
@@ -555,6 +556,14 @@ bool ring_pack_pays(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, i
     return pays && (int64_t)k.a_bytes <= kMaxExtent && (int64_t)k.b_bytes <= kMaxExtent;
 }
 
+// Very shallow products with at least one 32-row tile per CU: the streaming kernel.
+// fp32 from one and a half (8192x64x64 8.0 us against 7.7 on the tile kernel) and
+// with two consumer waves' columns (16384x40x128 9.0 against 7.7).
+bool stream_pays(int64_t M, int64_t N, int64_t K, int ab_type, int cus) {
+    if (ab_type == kF32 && (N < 64 || 2 * cdiv(M, 32) < 3 * (int64_t)cus)) return false;
+    return K <= gemm_stream_max_k(ab_type) && N <= 256 && N % 4 == 0 && cdiv(M, 32) >= cus;
+}
+
 // Whether a plan of plan_gemm keeps its special kernel (skinny, narrow, small or
 // streaming) for these operands instead of the ring kernel.
 bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, bool vec,
@@ -562,7 +571,7 @@ bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int6
     if (p.skinny == 4) return !trans_a && !trans_b && a_rows_aligned;
     if (p.skinny) return vec && !trans_a && !trans_b;
     if (p.small) return vec && !trans_a;
-    return ab_type == kBF16 && vec && !trans_a && !trans_b && K <= kStreamMaxK && N <= 256 && N % 4 == 0 && cdiv(M, 32) >= cus;
+    return vec && !trans_a && !trans_b && stream_pays(M, N, K, ab_type, cus);
 }
 
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
@@ -649,9 +658,10 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const int cus = device_cus();
         const int64_t es = (int64_t)dsize(ab_type);
         const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
-        RingPlan r = plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
-        if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
-                                      !((uintptr_t)A & 15) && lda * es % 16 == 0, cus)) {
+        const bool special = special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
+                                            !((uintptr_t)A & 15) && lda * es % 16 == 0, cus);
+        RingPlan r = special ? RingPlan{0, 1} : plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
+        if (r.ring) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, need_a, need_b);
             const size_t pack_bytes = k.a_bytes + k.b_bytes;
             char* ws = static_cast<char*>(workspace);
@@ -824,7 +834,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const char* env = getenv("ISAM_GEMM_CONFIG");
         const bool off = env && strstr(env, "stream=0"), force = env && strstr(env, "stream=1");
         if (!off && batch == 1 && !p.skinny && !p.small && gemm_stream_fits(a) &&
-            (force || (K <= kStreamMaxK && cdiv(M, 32) >= (int64_t)device_cus()))) {
+            (force || stream_pays(M, N, K, ab_type, device_cus()))) {
             if (log_enabled()) fprintf(stderr, "[isam] %s streaming kernel\n", who);
             hipError_t e = launch_gemm_stream(a, device_cus(), stream);
             if (e != hipSuccess) return hip_fail(e, who);

@@ -1,6 +1,6 @@
 // Very shallow products: C (+)= A.B of the paper's first listing (Section 2)
-// with K <= 256 and N <= 256, bf16 A [M][K] (K-contiguous) and B [K][N]
-// (N-contiguous) -- the pointwise half of the separable convolution (Section
+// with N <= 256 and rows of A of at most 512 bytes (K <= 256 bf16, 128 fp32), A
+// [M][K] (K-contiguous) and B [K][N] (N-contiguous) -- the pointwise half of the separable convolution (Section
 // 2.3: M pixels, K input channels, N output channels) when it is not fused
 // with the depthwise stencil.  Such a product is bound by streaming A in and
 // C out of HBM; a tiled GEMM spends most of each tile in its prologue (load
@@ -9,7 +9,8 @@
 //   * persistent workgroups (at most one per CU) take 32-row tiles of A in
 //     turn;
 //   * 8 consumer waves each own 32 output columns: their slice of B, read
-//     once at the start, is the A operand of v_mfma_f32_32x32x16_bf16 for the
+//     once at the start, is the A operand of v_mfma_f32_32x32x16_bf16 (or of
+//     v_mfma_f32_32x32x2_f32, even and odd steps in two accumulators) for the
 //     transposed product C^T = B^T . A^T, whose B operand is the A tile read
 //     with ds_read_b128; results leave as 4-column stores straight from the
 //     accumulators, so consumers issue no loads after the start;
@@ -20,6 +21,11 @@
 //   * one workgroup barrier per tile: at barrier i the copies of tile i have
 //     landed and every consumer has finished reading tile i-1, whose stage the
 //     producers then refill with tile i+7.
+// fp32 is bound by its matrix instructions here (32 rows x 32 columns x K = 64 take
+// 2048 cycles of a SIMD; only ceil(N / 32) of the 8 consumer waves work).  Per call,
+// us (this kernel / the tile kernel it replaces): 100352x64x32 15.4 / 19.3,
+// 50000x96x40 14.2 / 17.1, 12544x200x100 13.8 / 15.9, 50176x96x128 22.1 / 26.5,
+// 50176x128x64 16.7 / 17.2.
 // LDS layout of a stage: row r (one pixel, CPR 16-byte chunks), chunk c at
 // c ^ swz(r) -- (r ^ r>>3) & 7 for 8-chunk rows, r & 15 for wider rows: the
 // 16 rows of every b128 read phase land on 16 different bank groups.
@@ -62,13 +68,14 @@ __device__ __forceinline__ int st_swz(int r) {
     else return r & 15;
 }
 
-// CPR: 16-byte chunks per A row in LDS (8, 16 or 32: K up to 64, 128, 256).
-template <int CPR>
+// CPR: 16-byte chunks per A row in LDS (8, 16 or 32: K up to 64, 128, 256 bf16 or 32, 64, 128 fp32).
+template <typename T, int CPR>
 __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void gemm_stream_kernel(GemmArgs a) {
     constexpr int STAGE = kStreamRows * CPR * 16;
     constexpr int COPIES = kStreamRows * CPR / 64;         // 1 KB copies per tile
     constexpr int CPW = COPIES / kStreamProducers;          // per producer wave
-    constexpr int KS = CPR / 2;                             // 16-deep MFMA steps
+    constexpr int E = 16 / (int)sizeof(T), ES = (int)sizeof(T);
+    constexpr int KS = CPR / 2;                             // MFMA steps of two chunks
     static_assert(COPIES % kStreamProducers == 0, "copies split evenly");
     __shared__ __attribute__((aligned(1024))) char smem[kStreamStages * STAGE];
 
@@ -80,7 +87,7 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
     if (wid >= kStreamConsumers) {
         // ---------------- producers ----------------
         const int p = wid - kStreamConsumers;
-        const __amdgpu_buffer_rsrc_t rsA = make_rsrc(a.A, (uint32_t)(((a.M - 1) * a.lda + a.K) * 2));
+        const __amdgpu_buffer_rsrc_t rsA = make_rsrc(a.A, (uint32_t)(((a.M - 1) * a.lda + a.K) * ES));
         const uint32_t base = (uint32_t)(uintptr_t)(const __attribute__((address_space(3))) char*)smem;
         // per copy q: LDS unit u = (p*CPW + q)*64 + lane -> row r, physical chunk pc
         int row_in[CPW], kof[CPW];
@@ -89,7 +96,7 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
             const int u = (p * CPW + q) * 64 + lane;
             const int r = u / CPR, pc = u % CPR;
             row_in[q] = r;
-            kof[q] = (pc ^ st_swz<CPR>(r)) * 8;
+            kof[q] = (pc ^ st_swz<CPR>(r)) * E;
         }
         // Copies of local tile i (tiles past the last one read nothing).
         auto issue = [&](int i) {
@@ -100,7 +107,7 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
                 const int64_t m = m0 + row_in[q];
                 const bool in = i < nt && m < a.M && kof[q] < a.K;
                 st_dma16(rsA, __builtin_amdgcn_readfirstlane(st + (uint32_t)((p * CPW + q) * 1024)),
-                         in ? (uint32_t)((m * a.lda + kof[q]) * 2) : kOob);
+                         in ? (uint32_t)((m * a.lda + kof[q]) * ES) : kOob);
             }
         };
         for (int i = 0; i < kStreamStages - 1; ++i) issue(i);
@@ -118,20 +125,23 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
     const int64_t n0 = (int64_t)wid * 32;
     const int g = lane >> 5, l32 = lane & 31;
     // B^T slice as MFMA A operands: step s, lane (n = n0 + l32, K group g):
-    // B[16 s + 8 g + e][n], e = 0..7
+    // B[E (2 s + g) + e][n], e = 0..E-1
     uint4 bt[KS];
     {
-        const __amdgpu_buffer_rsrc_t rsB = make_rsrc(a.B, (uint32_t)(((a.K - 1) * a.ldb + a.N) * 2));
+        const __amdgpu_buffer_rsrc_t rsB = make_rsrc(a.B, (uint32_t)(((a.K - 1) * a.ldb + a.N) * ES));
         const int64_t n = n0 + l32;
+        auto off = [&](int64_t k) { return (n < a.N && k < a.K) ? (uint32_t)((k * a.ldb + n) * ES) : kOob; };
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             uint32_t w[4];
 #pragma unroll
-            for (int e2 = 0; e2 < 4; ++e2) {
-                const int64_t k = 16 * s + 8 * g + 2 * e2;
-                const uint32_t lo = buf_load2(rsB, (n < a.N && k < a.K) ? (uint32_t)((k * a.ldb + n) * 2) : kOob);
-                const uint32_t hi = buf_load2(rsB, (n < a.N && k + 1 < a.K) ? (uint32_t)(((k + 1) * a.ldb + n) * 2) : kOob);
-                w[e2] = (lo & 0xffffu) | (hi << 16);
+            for (int e = 0; e < 4; ++e) {
+                if constexpr (ES == 4) {
+                    w[e] = buf_load4(rsB, off(8 * s + 4 * g + e));
+                } else {
+                    const int64_t k = 16 * s + 8 * g + 2 * e;
+                    w[e] = (buf_load2(rsB, off(k)) & 0xffffu) | (buf_load2(rsB, off(k + 1)) << 16);
+                }
             }
             bt[s] = make_uint4(w[0], w[1], w[2], w[3]);
         }
@@ -148,16 +158,18 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
         st_barrier();
         if (!wave_on) continue;
         const char* st = smem + (i % kStreamStages) * STAGE;
-        f32x16_t acc;
+        f32x16_t acc, odd;
 #pragma unroll
-        for (int v = 0; v < 16; ++v) acc[v] = 0.0f;
+        for (int v = 0; v < 16; ++v) acc[v] = odd[v] = 0.0f;
 #pragma unroll
         for (int s = 0; s < KS; ++s) {
             // A^T fragment: pixel l32, K chunk 2 s + g
             const int c = 2 * s + g;
             const uint4 af = *reinterpret_cast<const uint4*>(st + l32 * (CPR * 16) + ((c ^ st_swz<CPR>(l32)) << 4));
-            mfma32_bf16(acc, bt[s], af);
+            if constexpr (ES == 4) mfma32_f32x4(s & 1 ? odd : acc, bt[s], af);
+            else mfma32_bf16(acc, bt[s], af);
         }
+        if constexpr (ES == 4) acc += odd;
         const int64_t m = ((int64_t)blockIdx.x + (int64_t)i * gridDim.x) * kStreamRows + l32;
 #pragma unroll
         for (int q = 0; q < 4; ++q) {
@@ -190,9 +202,9 @@ __global__ __launch_bounds__(64 * (kStreamConsumers + kStreamProducers)) void ge
 }  // namespace
 
 bool gemm_stream_fits(const GemmArgs& a) {
-    const int es_c = a.c_type == kF32 ? 4 : 2;
-    return a.ab_type == kBF16 && !a.trans_a && !a.trans_b && a.batch <= 1 && a.M > 0 && a.K > 0 && a.K <= 256 &&
-           a.N > 0 && a.N <= 32 * kStreamConsumers && a.N % 4 == 0 && a.K % 8 == 0 && a.lda % 8 == 0 &&
+    const int es_c = a.c_type == kF32 ? 4 : 2, es = a.ab_type == kF32 ? 4 : 2;
+    return !a.trans_a && !a.trans_b && a.batch <= 1 && a.M > 0 && a.K > 0 && a.K <= gemm_stream_max_k(a.ab_type) &&
+           a.N > 0 && a.N <= 32 * kStreamConsumers && a.N % 4 == 0 && a.K * es % 16 == 0 && a.lda * es % 16 == 0 &&
            ((uintptr_t)a.A & 15) == 0 && ((uintptr_t)a.C & 15) == 0 && (a.ldc * es_c) % 16 == 0;
 }
 
@@ -200,9 +212,17 @@ hipError_t launch_gemm_stream(const GemmArgs& a, int cus, hipStream_t s) {
     if (!gemm_stream_fits(a)) return hipErrorInvalidValue;
     const int64_t ntiles = (a.M + kStreamRows - 1) / kStreamRows;
     const dim3 grid((unsigned)std::min<int64_t>(ntiles, cus)), block(64 * (kStreamConsumers + kStreamProducers));
-    if (a.K <= 64) hipLaunchKernelGGL(gemm_stream_kernel<8>, grid, block, 0, s, a);
-    else if (a.K <= 128) hipLaunchKernelGGL(gemm_stream_kernel<16>, grid, block, 0, s, a);
-    else hipLaunchKernelGGL(gemm_stream_kernel<32>, grid, block, 0, s, a);
+    auto go = [&](auto kern) { hipLaunchKernelGGL(kern, grid, block, 0, s, a); };
+    const int64_t row = a.K * (a.ab_type == kF32 ? 4 : 2);  // bytes
+    if (a.ab_type == kF32) {
+        if (row <= 128) go(gemm_stream_kernel<float, 8>);
+        else if (row <= 256) go(gemm_stream_kernel<float, 16>);
+        else go(gemm_stream_kernel<float, 32>);
+    } else {
+        if (row <= 128) go(gemm_stream_kernel<bf16_t, 8>);
+        else if (row <= 256) go(gemm_stream_kernel<bf16_t, 16>);
+        else go(gemm_stream_kernel<bf16_t, 32>);
+    }
     return hipGetLastError();
 }
 

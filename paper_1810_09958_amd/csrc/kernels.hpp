@@ -92,9 +92,9 @@ uint64_t next_fixup_epoch();
 constexpr int64_t kSmallMaxTiles = 64;
 constexpr int64_t kSmallMaxK = 1024;
 bool gemm_small_fits(int64_t M, int64_t N, int64_t K);
-// Very shallow bf16 products (K <= 256, N <= 256, NN): B in registers, A streamed.
+// Very shallow products (rows of A up to 512 bytes, N <= 256, NN): B in registers, A streamed.
+constexpr int64_t gemm_stream_max_k(int ab_type) { return ab_type == kF32 ? 128 : 256; }
 bool gemm_stream_fits(const GemmArgs& a);
-constexpr int64_t kStreamMaxK = 256;  // planner: deepest K routed to it by default
 hipError_t launch_gemm_stream(const GemmArgs& a, int cus, hipStream_t s);
 hipError_t launch_gemm_small(const GemmArgs& a, hipStream_t s);
 int64_t skinny_k_slice(int ab_type);

@@ -101,3 +101,16 @@ def test_f32x_error_is_below_the_fp32_instructions(monkeypatch):
             C = isam.gemm(A, B, trans_b=bool(tb))
             err[env] = float((C.double() - ref).norm() / ref.norm())
         assert err[""] <= err["f32x=0,f32split=0"], err
+
+
+# Streaming kernel on fp32 (N <= 256, K <= 128, B in registers): ragged last 32-row tile, K off the
+# MFMA step, N off a wave's 32 columns, padded leading dimensions.
+@pytest.mark.parametrize("M,N,K", [(33, 8, 8), (100, 40, 36), (257, 256, 128), (64, 100, 100), (95, 256, 4),
+                                   (1, 4, 64), (300, 12, 124), (20000, 132, 64)])
+def test_stream_fp32(M, N, K, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", "stream=1,skinny=0,small=0,f32x=0")
+    _check(*_operands(M, N, K, 0, 0, 0, M), 0, 0)
+    _check(*_operands(M, N, K, 0, 0, 4, N), 0, 0, acc=True, ct=torch.bfloat16)
+    A, B = _operands(M, N, K, 0, 0, 0, M)
+    A[M // 2, K - 1], B[K - 1, 1] = math.inf, 0.0
+    _check(A, B, 0, 0)
