@@ -1,36 +1,41 @@
 // fp32 products of the paper's first listing (Section 2) on the bf16 matrix
 // cores, any operand layout with 16-byte aligned rows.  Each operand value is
-// the sum of three bf16 terms (split3_pair in common.hpp) and a product the
-// six bf16 products hh + hm + mh + hl + lh + mm: six MFMAs of 1024 FLOP per
-// cycle and SIMD for one of 64, so 2.7 times the fp32 matrix rate.  The terms
+// the sum of three bf16 terms (split3_pair in common.hpp) and a product eight of
+// the nine bf16 products, all but ll (2^-32 of the product): eight MFMAs of 1024
+// FLOP per cycle and SIMD for one of 64, so twice the fp32 matrix rate.  The terms
 // are formed in registers, from fp32 tiles in LDS: nothing but the operands is
 // read from memory and no copy of the terms is written.
 //
+// Eight and not six: without ml and lm a product is off by up to 2^-24 of itself
+// before the result is rounded, so a sum that holds one non-zero product (a
+// diagonal scaling, a selection) is off by up to 1.68 half units in the last place
+// and 4 % of such results are not the nearest; with them 1.004 and 0.15 % (the fp32
+// instructions: 1 and none).  They cost a tenth of the time (2048x1024x1024 32.9 ->
+// 35.9 us, 1536x1536x1536 63.5 -> 67, 2048x4096x4096 379 -> 430).
+//
 // What bounds it: forming the terms takes 11 vector instructions per two
 // values, 44 per MFMA operand block, so a wave of 2 x 2 blocks issues about 200
-// vector instructions (800 cycles) for 24 MFMAs (768 cycles): the two have to
+// vector instructions (800 cycles) for 32 MFMAs (1024 cycles): the two have to
 // run side by side.  So:
 //   * a wave owns 64 x 64 of the tile and one 16-deep step of each K tile; the
 //     other waves on its SIMD take other K steps of the same block (WK), so no
 //     value is split more often than the 2 x 2 block needs, and their MFMAs
 //     fill each other's gaps.  The WK sums are added through LDS at the end;
-//   * of the four operand blocks of a step one is split while the six MFMAs of
+//   * of the four operand blocks of a step one is split while the eight MFMAs of
 //     a block pair run: (A0,B0) with A1, (A1,B0) with B1, (A0,B1) with B0 of
 //     the next K tile, (A1,B1) with A0 of the next.  Four split blocks are live
 //     at a time, as many as one step needs;
-//   * the five small products have an accumulator of their own, added at the end:
+//   * the seven small products have an accumulator of their own, added at the end:
 //     a result is rounded once per 16 values of K at its full size, where the
 //     fp32 matrix instructions round at least 8 times, so the error against
 //     64 bits is smaller than theirs (2048x1024x1024: 9.8e-8 of the result's norm
-//     against 1.9e-7, 512x512x4096 1.1e-7 against 5.7e-7).
-// Per call, fp32, us (this kernel / what it replaces: the fp32 tile kernel, or
-// split copies in memory for 2048x1024x1024 NT): 2048x1024x1024 NT 31 / 62,
-// 1536x768x3072 TN 56 / 143, 1500x1500x1499 67 / 135, 1000^3 24 / 35,
-// 512x512x4096 27 / 37, 4096x512x512 20 / 29, 8192x256x256 14 / 16.  With the whole
-// chip busy it runs at 1.1 PFLOP/s of bf16 products, the rate at which random
-// values are held by power; one workgroup alone takes 1.1 us per 128x128x32
-// step, 2.9 per two steps with all CUs busy.  Terms by masks instead of
-// conversions cost the same time and, truncated, more error.
+//     against 5.7e-7, 512x512x4096 1.1e-7 against 5.7e-7).
+// Per call, fp32, us (this kernel / the fp32 tile kernel): 2048x1024x1024 NT 36 /
+// 48, 1536x768x3072 TN 61 / 145, 1536x1536x1536 TN 67 / 124, 1000^3 25 / 34,
+// 512x512x4096 29 / 37, 4096x512x512 21 / 27, 8192x256x256 14.2 / 15.9.  With the whole
+// chip busy it runs at 1.25 PFLOP/s of bf16 products, the rate at which random
+// values are held by power.  Terms by masks instead of conversions cost the same
+// time and, truncated, more error.
 // The copies into an LDS ring and the K slices summed by the last arrival are
 // those of the bf16 kernel (gemm_ring.hpp).  K tiles are 32 deep per sub-block
 // (a K-contiguous row is one 128-byte line, as 64 bf16 values are there); rows
@@ -159,7 +164,7 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
     const OpB ob(a.B, t.b_bytes, a.ldb, a.N, n0, wid, lane);
     const uint32_t sbase = lds_addr_of(smem);
 
-    f32x16_t acc[2][2], low[2][2];  // hh; the five small products
+    f32x16_t acc[2][2], low[2][2];  // hh; the seven small products
     static_for<2>([&](auto i_) {
         static_for<2>([&](auto j) {
             static_for<16>([&](auto v) { acc[i_][j][decltype(v)::value] = low[i_][j][decltype(v)::value] = 0.0f; });
@@ -184,17 +189,14 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
     auto read_b = [&](auto b, const char* s) { OpB::read(rb[b], s + OpA::BYTES, wn * 64 + b * 32, wk, lane); };
     using C0 = std::integral_constant<int, 0>;
     using C1 = std::integral_constant<int, 1>;
-    // Smallest terms first: (A, B) = (m,m) (l,h) (h,l) (m,h) (h,m), then (h,h).
+    // Smallest terms first: (A, B) = (l,m) (m,l) (m,m) (l,h) (h,l) (m,h) (h,m), then (h,h).
     auto block = [&](auto ic, auto jc, F32xTerms& o, const float (&src)[8], float& mx, auto&& extra) {
-        constexpr int TI[6] = {1, 2, 0, 1, 0, 0}, TJ[6] = {1, 0, 2, 0, 1, 0};
-        static_for<6>([&](auto mc) {
+        constexpr int TI[8] = {2, 1, 1, 2, 0, 1, 0, 0}, TJ[8] = {1, 2, 1, 0, 2, 0, 1, 0};
+        static_for<8>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
-            mfma32_bf16(m < 5 ? low[ic][jc] : acc[ic][jc], ta[ic].op(TI[m]), tb[jc].op(TJ[m]));
-            if constexpr (m == 0) f32x_split<0>(o, src, mx);
-            else if constexpr (m == 1) f32x_split<1>(o, src, mx);
-            else if constexpr (m == 3) f32x_split<2>(o, src, mx);
-            else if constexpr (m == 4) f32x_split<3>(o, src, mx);
-            else extra(std::integral_constant<int, m / 5>{});
+            mfma32_bf16(m < 7 ? low[ic][jc] : acc[ic][jc], ta[ic].op(TI[m]), tb[jc].op(TJ[m]));
+            if constexpr (m % 2 == 0) f32x_split<m / 2>(o, src, mx);
+            else if constexpr (m == 1 || m == 5) extra(std::integral_constant<int, m / 5>{});
             __builtin_amdgcn_sched_barrier(0);
         });
     };

@@ -10,8 +10,8 @@ import paper_1810_09958_amd as isam
 
 
 def _tol(K):
-    # Of sum |a||b|: the dropped terms (below 2^-23), the 32-bit sums (one rounding per 16 values
-    # of K, the five small products' far below, at most 24 when the K steps and slices are added)
+    # Of sum |a||b|: the terms the kernels drop (at most 2^-23), the 32-bit sums (one rounding per 16
+    # values of K, the small products' far below, at most 24 when the K steps and slices are added)
     # and the result's.
     return 2.0 ** -23 + (K / 16 + 26) * 2.0 ** -24
 
@@ -101,6 +101,19 @@ def test_f32x_error_is_below_the_fp32_instructions(monkeypatch):
             C = isam.gemm(A, B, trans_b=bool(tb))
             err[env] = float((C.double() - ref).norm() / ref.norm())
         assert err[""] <= err["f32x=0,f32split=0"], err
+
+
+# One non-zero product per result (a diagonal operand): the fp32 product rounded once, as the fp32
+# instructions give it, but for the dropped ll and the roundings of the small products' sum, each
+# below 2^-8 of a half unit in the last place.
+@pytest.mark.parametrize("ring,rs", [(1, 1), (2, 3), (3, 1)])
+def test_f32x_single_products(ring, rs, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs={rs},skinny=0,small=0")
+    _, B = _operands(256, 512, 256, 0, 0, 0, 4)
+    d = torch.randn(256, device="cuda", generator=torch.Generator(device="cuda").manual_seed(7))
+    ref = d.double()[:, None] * B.double()
+    for C in (isam.gemm(torch.diag(d), B), isam.gemm(B.t().contiguous(), torch.diag(d)).t()):
+        assert bool(((C.double() - ref).abs() <= 1.01 * 2.0 ** -24 * ref.abs()).all())
 
 
 # Streaming kernel on fp32 (N <= 256, K <= 128, B in registers): ragged last 32-row tile, K off the
