@@ -13,9 +13,9 @@
 // instructions: 1 and none).  They cost a tenth of the time (2048x1024x1024 32.9 ->
 // 35.9 us, 1536x1536x1536 63.5 -> 67, 2048x4096x4096 379 -> 430).
 //
-// What bounds it: forming the terms takes 11 vector instructions per two
-// values, 44 per MFMA operand block, so a wave of 2 x 2 blocks issues about 200
-// vector instructions (800 cycles) for 32 MFMAs (1024 cycles): the two have to
+// What bounds it: forming the terms takes 13 vector instructions per two
+// values, 52 per MFMA operand block, so a wave of 2 x 2 blocks issues about 230
+// vector instructions (920 cycles) for 32 MFMAs (1024 cycles): the two have to
 // run side by side.  So:
 //   * a wave owns 64 x 64 of the tile and one 16-deep step of each K tile; the
 //     other waves on its SIMD take other K steps of the same block (WK), so no
@@ -42,15 +42,25 @@
 // along M or N are read one value per lane, rows k and k + 8 (the two halves of
 // a wave) 32 banks apart.
 //
-// Range: a value of 2^60 or more (an infinity among them), or rows whose largest
-// value is below 2^-90 (their last terms are bf16 denormals), do not split.
-// Every lane keeps the largest magnitude of each row it reads; a workgroup that
-// saw either forms its tile again with fp32 matrix instructions.
+// Range: the operands are scaled by 2^24 while they are split, so the terms of every
+// value down to the smallest denormal (2^-149) are normal bf16 numbers and exact,
+// whatever stands beside it in its row; unscaled, a value below about 2^-109 loses
+// its low terms, and 2^-120 times 2^27 came out with 14 good bits.  The sums are
+// scaled back by 2^-48 at the end; products of values below 2^28 stay under 2^104
+// scaled, so 2^23 of them can be added.  The scaling costs two of the 13 vector
+// instructions per pair (2048x1024x1024 36.2 -> 37.6 us, 1536x1536x1536 66 -> 68).  A value of
+// 2^28 or more (an infinity among them) is not split: every lane keeps the largest
+// magnitude it reads, and a workgroup that saw one forms its tile again with fp32
+// matrix instructions.
 #pragma once
 
 #include "gemm_ring.hpp"
 
 namespace isam {
+
+constexpr float kF32xScale = 0x1p24f;     // on both operands while they are split
+constexpr float kF32xUnscale = 0x1p-48f;  // on the sums
+constexpr float kF32xLimit = 0x1p28f;     // a value from here on sends its tile to the fp32 instructions
 
 // One fp32 operand of a workgroup's tile: ROWS values of M / N x 32 SUB of K.
 template <int ROWS, bool KC, int NW, int SUB>
@@ -120,12 +130,12 @@ struct F32xTerms {
     __device__ __forceinline__ uint4 op(int i) const { return make_uint4(t[i][0], t[i][1], t[i][2], t[i][3]); }
 };
 
-// Pair P of a block into terms; `top` keeps the lane's largest magnitude (a NaN
+// Pair P of a block, scaled, into terms; `top` keeps the lane's largest magnitude (a NaN
 // drops out of the maximum and stays one in the terms).
 template <int P>
 __device__ __forceinline__ void f32x_split(F32xTerms& o, const float (&x)[8], float& top) {
     uint32_t w[3];
-    split3_pair(x[2 * P], x[2 * P + 1], w);
+    split3_pair(x[2 * P] * kF32xScale, x[2 * P + 1] * kF32xScale, w);
     static_for<3>([&](auto i) { o.t[i][P] = w[i]; });
     asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(x[2 * P]), "v"(x[2 * P + 1]));
 }
@@ -235,10 +245,10 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
     }
     vm_wait<0>();  // copies of tiles past the end still write (zeros) into LDS
     bool bad = false;
-    static_for<4>([&](auto q) { bad |= top[q] >= 0x1p60f || (top[q] < 0x1p-90f && top[q] > 0.0f); });
+    static_for<4>([&](auto q) { bad |= top[q] >= kF32xLimit; });
     const bool again = __syncthreads_or(bad ? 1 : 0) != 0;
     if (!again) {
-        static_for<2>([&](auto i_) { static_for<2>([&](auto j) { acc[i_][j] += low[i_][j]; }); });
+        static_for<2>([&](auto i_) { static_for<2>([&](auto j) { acc[i_][j] = (acc[i_][j] + low[i_][j]) * kF32xUnscale; }); });
         auto piece = [&](int k, auto c) { return reinterpret_cast<f32x4_t*>(smem + (k * NB + wb) * 16384 + c * 1024 + lane * 16); };
         if (wk) {
             static_for<16>([&](auto c) {

@@ -71,8 +71,8 @@ def test_f32x_planned(ta, tb, M, N, K, monkeypatch):
     assert bool(((y.reshape(-1, 384) - ref).abs() <= _tol(5 * 256) * S).all())
 
 
-# Values that do not split into bf16 terms: infinities, NaNs, magnitudes from 2^60 and rows below
-# 2^-90.  The workgroups that read them form their tiles in fp32.
+# Values that do not split into bf16 terms (infinities, NaNs, magnitudes from 2^28: the workgroups
+# that read them form their tiles in fp32), and rows and columns of tiny values.
 @pytest.mark.parametrize("ring,rs", [(1, 1), (1, 3), (2, 1), (2, 4), (3, 2)])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_f32x_range(ring, rs, ta, tb, monkeypatch):
@@ -114,6 +114,24 @@ def test_f32x_single_products(ring, rs, monkeypatch):
     ref = d.double()[:, None] * B.double()
     for C in (isam.gemm(torch.diag(d), B), isam.gemm(B.t().contiguous(), torch.diag(d)).t()):
         assert bool(((C.double() - ref).abs() <= 1.01 * 2.0 ** -24 * ref.abs()).all())
+
+
+# Tiny values beside ordinary ones in the same row, where the ordinary ones meet zeros: down to
+# denormals, and up to the largest values that are split.  The tolerance is that of ordinary values
+# (no allowance for products below 2^-126: there are none).
+@pytest.mark.parametrize("ring,rs", [(1, 1), (2, 3), (3, 1)])
+@pytest.mark.parametrize("small", [-100, -115, -126, -140])
+def test_f32x_tiny_beside_ordinary(ring, rs, small, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs={rs},skinny=0,small=0")
+    A, B = _operands(132, 136, 200, 0, 0, 0, -small)
+    A.clamp_(-4, 4).mul_(2.0 ** small)
+    B.clamp_(-4, 4).mul_(2.0 ** 25)
+    A[:, ::7] = 1.0
+    B[::7] = 0.0
+    for C, ref, S in ((isam.gemm(A, B), A.double() @ B.double(), A.double().abs() @ B.double().abs()),
+                      (isam.gemm(B.t().contiguous(), A.t().contiguous()), B.double().t().contiguous() @ A.double().t().contiguous(),
+                       B.double().abs().t().contiguous() @ A.double().abs().t().contiguous())):
+        assert bool(((C.double() - ref).abs() <= _tol(200) * S).all())
 
 
 # Streaming kernel on fp32 (N <= 256, K <= 128, B in registers): ragged last 32-row tile, K off the
