@@ -574,6 +574,17 @@ bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int6
     return vec && !trans_a && !trans_b && stream_pays(M, N, K, ab_type, cus);
 }
 
+// Whether a product that could run on split copies of its operands (split_plan) takes
+// the kernel that forms the terms in registers instead: small grids where its plan
+// pays, with operands that are aligned or can be copied into `room` bytes of
+// workspace.  Otherwise the split copies keep it, which take any alignment.
+bool f32x_over_split(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a, bool need_b, size_t room, int cus) {
+    if (!f32x_grid(M, N, cus) || !plan_ring(M, N, K, kF32, !need_a && !need_b, 1, cus, true).ring) return false;
+    if (!need_a && !need_b) return true;
+    const RingPack k = ring_pack(trans_a, trans_b, M, N, K, kF32, need_a, need_b);
+    return k.a_bytes + k.b_bytes <= room && ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k);
+}
+
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
                             const void* A, int64_t lda, const void* B, int64_t ldb, int accumulate,
                             int c_type, const void* C, int64_t ldc, const char* who) {
@@ -629,7 +640,9 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         char* ws = static_cast<char*>(workspace);
         const size_t split_bytes = k.a_bytes + k.b_bytes;
-        if (k.pays && !f32x_grid(M, N, device_cus()) && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes) {
+        if (k.pays && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes &&
+            !f32x_over_split(trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
+                             pack_b_needed(trans_b, N, K, ab_type, B, ldb), workspace_bytes, device_cus())) {
             const int64_t es = (int64_t)dsize(ab_type);
             const size_t a_b = (size_t)(((M - 1) * lda + K) * es);
             const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
@@ -856,13 +869,23 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
     // Rows that the sizes alone make unfit for 16-byte copies (a contiguous
     // dimension off the vector width), and bf16 A given as [K][M]: room to pack
     // them, and what the packed product then uses.
-    if (ab_type == ISAM_F32) {
-        const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
-        if (k.pays && !f32x_grid(M, N, cus))
-            return std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
-    }
     const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
     const bool a_off = (trans_a ? M : K) % E != 0, b_off = (trans_b ? K : N) % E != 0;
+    if (ab_type == ISAM_F32) {
+        const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
+        if (k.pays) {
+            // Split copies, or the kernel that forms the terms in registers and, as the
+            // split copies take operands of any alignment, room for copies of both.
+            const RingPack both = ring_pack(trans_a, trans_b, M, N, K, kF32, true, true);
+            const size_t copies = both.a_bytes + both.b_bytes;
+            if (!f32x_over_split(trans_a, trans_b, M, N, K, a_off, b_off, copies, cus) ||
+                !f32x_over_split(trans_a, trans_b, M, N, K, true, true, copies, cus))
+                ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
+            else
+                ws = std::max(ws, copies + gemm_ring_ws_bytes(plan_ring(M, N, K, kF32, false, 1, cus, true), M, N));
+            if (!f32x_grid(M, N, cus)) return ws;
+        }
+    }
     {
         const RingPlan r = plan_ring(M, N, K, ab_type, !a_off && !b_off, 1, cus, true);
         if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, !a_off && !b_off, K % E == 0, cus)) {

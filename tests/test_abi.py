@@ -139,6 +139,14 @@ def test_gemm_workspace_query_covers_fp32_split(L, monkeypatch):
     assert L.isam_gemm_workspace_size(0, 0, 512, 512, 512, F32, F32) == small
 
 
+def test_gemm_workspace_query_keeps_room_for_unaligned_fp32(L, monkeypatch):
+    # Below one 128 x 128 tile per compute unit the terms are formed in registers; operands off 16
+    # bytes are copied first, and the query has room for both (or for the split copies).
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    for M, N, K, tb in ((2048, 1024, 1024, 1), (1536, 1536, 1536, 0), (1144, 1776, 928, 0), (1024, 2048, 1001, 1)):
+        assert L.isam_gemm_workspace_size(0, tb, M, N, K, F32, F32) >= (M + N) * K * 4
+
+
 def test_gemm_split_workspace_must_not_overlap_operands(L, monkeypatch):
     monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
     M, N, K = 4096, 4096, 4096

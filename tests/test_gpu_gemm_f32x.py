@@ -71,6 +71,28 @@ def test_f32x_planned(ta, tb, M, N, K, monkeypatch):
     assert bool(((y.reshape(-1, 384) - ref).abs() <= _tol(5 * 256) * S).all())
 
 
+# Products that the split copies (any alignment) served: with bases and leading dimensions off 16
+# bytes and the queried workspace they run on the terms too, not element by element.
+@pytest.mark.parametrize("tb", [0, 1])
+@pytest.mark.parametrize("off_a,off_b", [(1, 0), (0, 1), (1, 1)])
+@pytest.mark.parametrize("M,N,K", [(2048, 1024, 1024), (1144, 1776, 928)])
+def test_fp32_unaligned_operands_run_on_terms(tb, off_a, off_b, M, N, K, monkeypatch, capfd):
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    monkeypatch.setenv("ISAM_LOG", "1")
+    A, B = _operands(M, N, K, 0, tb, 0, 3)
+
+    def shift(x, off):  # rows one value longer, from an odd address
+        if not off:
+            return x
+        w = torch.zeros(x.shape[0] * (x.shape[1] + 1) + 1, device="cuda")[1:].view(x.shape[0], x.shape[1] + 1)[:, : x.shape[1]]
+        w.copy_(x)
+        return w
+
+    _check(shift(A, off_a), shift(B, off_b), 0, tb)
+    log = capfd.readouterr().err
+    assert "ring kernel" in log or "fp32 split into bf16 terms" in log, log
+
+
 # Values that do not split into bf16 terms (infinities, NaNs, magnitudes from 2^28: the workgroups
 # that read them form their tiles in fp32), and rows and columns of tiny values.
 @pytest.mark.parametrize("ring,rs", [(1, 1), (1, 3), (2, 1), (2, 4), (3, 2)])
