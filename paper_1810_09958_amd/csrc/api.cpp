@@ -443,18 +443,30 @@ bool pack_b_needed(int trans_b, int64_t N, int64_t K, int ab_type, const void* B
 // Cost of the fp32 kernel on bf16 terms (gemm_f32x.hpp), us, and of the kernels
 // it stands beside, fitted to a sweep on MI355X.  A workgroup holds its CU
 // alone: per round of workgroups the start and end of one and its 64-deep K
-// tiles (128x128 / 64x64 / 128x64 at 2.9 / 0.78 / 1.45 us with the whole chip
-// busy, which power limits: 1.1 PFLOP/s of bf16 products).
-double f32x_us(int ring, int64_t iters, int64_t per_cu, int64_t sp) {
-    static const double fixed[3] = {8.5, 6.8, 8.0}, rate[3] = {2.9, 0.78, 1.45};
+// tiles, which take 128x128 / 64x64 / 128x64 workgroups 2.3 / 0.84 / 1.2 us when
+// few CUs are busy and 3.4 / 0.98 / 1.82 when all are (power: 1.25 PFLOP/s of bf16
+// products; busy: share of the rounds' CUs that have a workgroup).
+double f32x_us(int ring, int64_t iters, int64_t wgs, int64_t sp, int cus) {
+    static const double fixed[3] = {8.5, 8.0, 9.0}, rate[3] = {2.3, 0.84, 1.2}, power[3] = {1.1, 0.14, 0.62};
+    const int64_t per_cu = cdiv(wgs, cus);
+    const double busy = (double)wgs / (double)(per_cu * cus);
     const double split = sp <= 1 ? 0.0 : ring == 2 ? 0.7 + 1.6 * (double)sp : 2.5 + 1.1 * (double)sp;
-    return (double)per_cu * (fixed[ring - 1] + rate[ring - 1] * (double)iters) + split;
+    return (double)per_cu * (fixed[ring - 1] + (rate[ring - 1] + power[ring - 1] * busy * busy) * (double)iters) + split;
 }
-// The fp32 tile kernel runs at about 95 TFLOP/s, element by element at about 40
-// (the term kernel then also copies the operands, 4 us).
-bool f32x_pays(double us, int64_t M, int64_t N, int64_t K, int64_t batch, bool aligned) {
+// The fp32 tile kernel runs at about 110 TFLOP/s (with 64x64 tiles 80 at one per CU,
+// 125 at more) over the CUs its rounds of tiles keep busy: 2048x1024x1024 45 us by
+// this model and 48 measured, 1536^3 123 / 123, 1000^3 31 / 34, 512x512x4096 33 / 37,
+// 4096x512x512 25.5 / 27.4, 8192x256x256 15.8 / 15.7, 1600x1200x400 19 / 20.  Element by
+// element it runs at about 40.
+double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, bool aligned, int cus) {
     const double flops = 2.0 * (double)batch * (double)M * (double)N * (double)K;
-    return us + (aligned ? 0.0 : 4.0) < 0.93 * (6.0 + flops / (aligned ? 95e6 : 40e6));
+    if (!aligned) return 6.0 + flops / 40e6;
+    if (p.skinny || p.small) p = plan_gemm(M, N, K, kF32, cus, /*allow_skinny=*/false);
+    int bm, bn, bk;
+    tile_dims(p.tile, kF32, &bm, &bn, &bk);
+    const int64_t wgs = batch * cdiv(M, bm) * cdiv(N, bn) * (batch > 1 ? 1 : p.k_splits);
+    const double busy = (double)wgs / (double)(cdiv(wgs, cus) * cus);
+    return 6.0 + flops / ((bm * bn >= 128 * 64 ? 110e6 : wgs > cus ? 125e6 : 80e6) * busy);
 }
 
 // bf16 products whose 128x128 tiles leave CUs idle run on the LDS-ring kernel
@@ -472,8 +484,10 @@ bool f32x_pays(double us, int64_t M, int64_t N, int64_t K, int64_t batch, bool a
 // tiles and rs=<n> the K slices; settings of the other kernels also switch it off.
 //
 // fp32 products take the same tiles and K slices on the kernel of gemm_f32x.hpp
-// (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size.
-RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus, bool may_split) {
+// (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size, where that beats the
+// tile kernel's plan p.
+RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus,
+                   bool may_split) {
     RingPlan none{0, 1};
     if (M <= 0 || N <= 0 || K <= 0) return none;
     const bool f32 = ab_type == kF32;
@@ -487,7 +501,11 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, i
         if ((q = strstr(env, f32 ? "f32x=" : "ring="))) force = std::min(f32 ? 3 : 2, atoi(q + 5));
         if ((q = strstr(env, "rs="))) force_s = atoi(q + 3);
     }
-    if (f32 && !force && !f32x_pays(f32x_us(2, 1, 1, 1), M, N, K, batch, aligned)) return none;  // not even at its least
+    // What the fp32 kernel has to beat (operands off 16 bytes are copied first: a launch
+    // and about 3 TB/s).
+    const double beat = f32 && !force ? 0.95 * f32_tile_us(p, M, N, K, batch, aligned, cus) -
+                                            (aligned ? 0.0 : 4.0 + 8.0 * (double)(M + N) * (double)K / 3e6) : 0.0;
+    if (f32 && !force && f32x_us(2, 1, 1, 1, cus) >= beat) return none;  // not even at its least
     if (!f32 && !force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
     RingPlan best = none;
     double best_us = 0;
@@ -499,8 +517,8 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, i
         const int64_t most = may_split ? std::max<int64_t>(1, std::min<int64_t>(force ? 255 : 8, nk / (force ? 1 : 4))) : 1;
         for (int64_t sp = 1; sp <= most; ++sp) {
             if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
-            const int64_t iters = cdiv(nk, sp), per_cu = cdiv(tiles * cdiv(nk, iters), cus);
-            const double us = f32 ? f32x_us(ring, iters, per_cu, sp) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
+            const int64_t iters = cdiv(nk, sp), wgs = tiles * cdiv(nk, iters), per_cu = cdiv(wgs, cus);
+            const double us = f32 ? f32x_us(ring, iters, wgs, sp, cus) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
                                         : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
                                               (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);
             if (!best.ring || us < best_us) {
@@ -509,7 +527,7 @@ RingPlan plan_ring(int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, i
             }
         }
     }
-    if (f32 && !force && !f32x_pays(best_us, M, N, K, batch, aligned)) return none;
+    if (f32 && !force && best_us >= beat) return none;
     return best;
 }
 
@@ -578,8 +596,9 @@ bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int6
 // the kernel that forms the terms in registers instead: small grids where its plan
 // pays, with operands that are aligned or can be copied into `room` bytes of
 // workspace.  Otherwise the split copies keep it, which take any alignment.
-bool f32x_over_split(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a, bool need_b, size_t room, int cus) {
-    if (!f32x_grid(M, N, cus) || !plan_ring(M, N, K, kF32, !need_a && !need_b, 1, cus, true).ring) return false;
+bool f32x_over_split(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a,
+                     bool need_b, size_t room, int cus) {
+    if (!f32x_grid(M, N, cus) || !plan_ring(p, M, N, K, kF32, !need_a && !need_b, 1, cus, true).ring) return false;
     if (!need_a && !need_b) return true;
     const RingPack k = ring_pack(trans_a, trans_b, M, N, K, kF32, need_a, need_b);
     return k.a_bytes + k.b_bytes <= room && ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k);
@@ -641,7 +660,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         char* ws = static_cast<char*>(workspace);
         const size_t split_bytes = k.a_bytes + k.b_bytes;
         if (k.pays && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes &&
-            !f32x_over_split(trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
+            !f32x_over_split(p, trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
                              pack_b_needed(trans_b, N, K, ab_type, B, ldb), workspace_bytes, device_cus())) {
             const int64_t es = (int64_t)dsize(ab_type);
             const size_t a_b = (size_t)(((M - 1) * lda + K) * es);
@@ -673,7 +692,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
         const bool special = special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
                                             !((uintptr_t)A & 15) && lda * es % 16 == 0, cus);
-        RingPlan r = special ? RingPlan{0, 1} : plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
+        RingPlan r = special ? RingPlan{0, 1} : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
         if (r.ring) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, need_a, need_b);
             const size_t pack_bytes = k.a_bytes + k.b_bytes;
@@ -682,7 +701,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
             const bool packs = pack_bytes > 0;
             const bool fits = !packs || (ws_ok && workspace_bytes >= pack_bytes && ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k));
             if (fits && r.splits > 1 && (!ws_ok || workspace_bytes < pack_bytes + gemm_ring_ws_bytes(r, M, N)))
-                r = plan_ring(M, N, K, ab_type, !need_a && !need_b, batch, cus, false);
+                r = plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, false);
             if (fits && r.ring) {
                 const size_t used = pack_bytes + gemm_ring_ws_bytes(r, M, N);
                 if (used) {
@@ -878,16 +897,16 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
             // split copies take operands of any alignment, room for copies of both.
             const RingPack both = ring_pack(trans_a, trans_b, M, N, K, kF32, true, true);
             const size_t copies = both.a_bytes + both.b_bytes;
-            if (!f32x_over_split(trans_a, trans_b, M, N, K, a_off, b_off, copies, cus) ||
-                !f32x_over_split(trans_a, trans_b, M, N, K, true, true, copies, cus))
+            if (!f32x_over_split(p, trans_a, trans_b, M, N, K, a_off, b_off, copies, cus) ||
+                !f32x_over_split(p, trans_a, trans_b, M, N, K, true, true, copies, cus))
                 ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
             else
-                ws = std::max(ws, copies + gemm_ring_ws_bytes(plan_ring(M, N, K, kF32, false, 1, cus, true), M, N));
+                ws = std::max(ws, copies + gemm_ring_ws_bytes(plan_ring(p, M, N, K, kF32, false, 1, cus, true), M, N));
             if (!f32x_grid(M, N, cus)) return ws;
         }
     }
     {
-        const RingPlan r = plan_ring(M, N, K, ab_type, !a_off && !b_off, 1, cus, true);
+        const RingPlan r = plan_ring(p, M, N, K, ab_type, !a_off && !b_off, 1, cus, true);
         if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, !a_off && !b_off, K % E == 0, cus)) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, a_off, b_off);
             if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k))

@@ -30,9 +30,9 @@
 //     fp32 matrix instructions round at least 8 times, so the error against
 //     64 bits is smaller than theirs (2048x1024x1024: 9.8e-8 of the result's norm
 //     against 5.7e-7, 512x512x4096 1.1e-7 against 5.7e-7).
-// Per call, fp32, us (this kernel / the fp32 tile kernel): 2048x1024x1024 NT 36 /
-// 48, 1536x768x3072 TN 61 / 145, 1536x1536x1536 TN 67 / 124, 1000^3 25 / 34,
-// 512x512x4096 29 / 37, 4096x512x512 21 / 27, 8192x256x256 14.2 / 15.9.  With the whole
+// Per call, fp32, us (this kernel / the fp32 tile kernel): 2048x1024x1024 NT 38 /
+// 48, 1536x768x3072 TN 64 / 145, 1536x1536x1536 TN 69 / 123, 1000^3 25 / 34,
+// 512x512x4096 29 / 36, 4096x512x512 22.5 / 27.4, 8192x256x256 15.9 / 15.6.  With the whole
 // chip busy it runs at 1.25 PFLOP/s of bf16 products, the rate at which random
 // values are held by power.  Terms by masks instead of conversions cost the same
 // time and, truncated, more error.
@@ -49,9 +49,15 @@
 // scaled back by 2^-48 at the end; products of values below 2^28 stay under 2^104
 // scaled, so 2^23 of them can be added.  The scaling costs two of the 13 vector
 // instructions per pair (2048x1024x1024 36.2 -> 37.6 us, 1536x1536x1536 66 -> 68).  A value of
-// 2^28 or more (an infinity among them) is not split: every lane keeps the largest
-// magnitude it reads, and a workgroup that saw one forms its tile again with fp32
-// matrix instructions.
+// 2^28 or more (an infinity among them) is not split: a wave that reads one scales
+// its sums back and goes on with fp32 matrix instructions for the rest of its K
+// steps, on the same LDS tiles and barriers, so such values cost at most what they
+// cost the fp32 tile kernel.  A whole column of 1e30, us (first K tile / last /
+// none / tile kernel): 2048x1024x1024 45 / 39 / 39 / 46, 1536x1536x1536 88 / 70 / 71 / 124,
+// 512x512x4096 32 / 29 / 29 / 37; forming the tile again afterwards took 245, 750 and 220.
+// The check needs the tile's fp32 blocks in registers before its first MFMA; it
+// stands at the end of the loop so that the loop has one exit (a second one made
+// the compiler copy and spill accumulators: 81 us for 39).
 #pragma once
 
 #include "gemm_ring.hpp"
@@ -60,7 +66,7 @@ namespace isam {
 
 constexpr float kF32xScale = 0x1p24f;     // on both operands while they are split
 constexpr float kF32xUnscale = 0x1p-48f;  // on the sums
-constexpr float kF32xLimit = 0x1p28f;     // a value from here on sends its tile to the fp32 instructions
+constexpr float kF32xLimit = 0x1p28f;     // values from here on take the fp32 instructions
 
 // One fp32 operand of a workgroup's tile: ROWS values of M / N x 32 SUB of K.
 template <int ROWS, bool KC, int NW, int SUB>
@@ -130,14 +136,18 @@ struct F32xTerms {
     __device__ __forceinline__ uint4 op(int i) const { return make_uint4(t[i][0], t[i][1], t[i][2], t[i][3]); }
 };
 
-// Pair P of a block, scaled, into terms; `top` keeps the lane's largest magnitude (a NaN
-// drops out of the maximum and stays one in the terms).
+// The largest magnitude of top and a lane's pair P (a NaN drops out of the maximum
+// and stays one in the terms).
 template <int P>
-__device__ __forceinline__ void f32x_split(F32xTerms& o, const float (&x)[8], float& top) {
+__device__ __forceinline__ void f32x_top(float& top, const float (&x)[8]) {
+    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(x[2 * P]), "v"(x[2 * P + 1]));
+}
+// Pair P of a block, scaled, into terms.
+template <int P>
+__device__ __forceinline__ void f32x_split(F32xTerms& o, const float (&x)[8]) {
     uint32_t w[3];
     split3_pair(x[2 * P] * kF32xScale, x[2 * P + 1] * kF32xScale, w);
     static_for<3>([&](auto i) { o.t[i][P] = w[i]; });
-    asm("v_max3_f32 %0, %0, |%1|, |%2|" : "+v"(top) : "v"(x[2 * P]), "v"(x[2 * P + 1]));
 }
 
 template <int BM, int BN, bool TA, bool TB, int WM, int WN, int WK, int ST, int OCC>
@@ -194,18 +204,18 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
 
     float ra[2][8], rb[2][8];   // fp32 blocks
     F32xTerms ta[2], tb[2];     // split blocks
-    float top[4] = {0.0f, 0.0f, 0.0f, 0.0f};
+    float top = 0.0f;  // largest magnitude seen
     auto read_a = [&](auto b, const char* s) { OpA::read(ra[b], s, wm * 64 + b * 32, wk, lane); };
     auto read_b = [&](auto b, const char* s) { OpB::read(rb[b], s + OpA::BYTES, wn * 64 + b * 32, wk, lane); };
     using C0 = std::integral_constant<int, 0>;
     using C1 = std::integral_constant<int, 1>;
     // Smallest terms first: (A, B) = (l,m) (m,l) (m,m) (l,h) (h,l) (m,h) (h,m), then (h,h).
-    auto block = [&](auto ic, auto jc, F32xTerms& o, const float (&src)[8], float& mx, auto&& extra) {
+    auto block = [&](auto ic, auto jc, F32xTerms& o, const float (&src)[8], auto&& extra) {
         constexpr int TI[8] = {2, 1, 1, 2, 0, 1, 0, 0}, TJ[8] = {1, 2, 1, 0, 2, 0, 1, 0};
         static_for<8>([&](auto mc) {
             constexpr int m = decltype(mc)::value;
             mfma32_bf16(m < 7 ? low[ic][jc] : acc[ic][jc], ta[ic].op(TI[m]), tb[jc].op(TJ[m]));
-            if constexpr (m % 2 == 0) f32x_split<m / 2>(o, src, mx);
+            if constexpr (m % 2 == 0) f32x_split<m / 2>(o, src);
             else if constexpr (m == 1 || m == 5) extra(std::integral_constant<int, m / 5>{});
             __builtin_amdgcn_sched_barrier(0);
         });
@@ -217,78 +227,102 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
     read_a(C1{}, smem);
     read_b(C1{}, smem);
     static_for<4>([&](auto p) {
-        f32x_split<decltype(p)::value>(ta[0], ra[0], top[0]);
-        f32x_split<decltype(p)::value>(tb[0], rb[0], top[2]);
+        f32x_split<decltype(p)::value>(ta[0], ra[0]);
+        f32x_split<decltype(p)::value>(tb[0], rb[0]);
     });
-    int cur = 0, next = 1;
-    for (int tt = 0; tt < nk; ++tt) {
-        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave holds its part of tile tt
+    int cur = 0, next = 1, tt = 0;
+    auto advance = [&] {
+        cur = next;
+        next = next + 1 == ST ? 0 : next + 1;
+    };
+    auto arrive = [&] {
+        __builtin_amdgcn_s_waitcnt(0xc07f);  // lgkmcnt(0): this wave holds its part of tile tt, in fp32
         vm_wait<(ST - 2) * PER_TILE>();      // and its share of tile tt + 1 has landed
         block_sync();                        // the same for every wave: tile tt's stage is free
+    };
+    auto large = [&] {
+        static_for<4>([&](auto p) {
+            static_for<2>([&](auto b) {
+                f32x_top<decltype(p)::value>(top, ra[b]);
+                f32x_top<decltype(p)::value>(top, rb[b]);
+            });
+        });
+        return __builtin_amdgcn_ballot_w64(top >= kF32xLimit) != 0;
+    };
+    arrive();
+    bool fp32 = large();
+    if (!fp32) do {
         const char* sn = smem + next * STAGE;
-        block(C0{}, C0{}, ta[1], ra[1], top[1], [&](auto e) {
+        block(C0{}, C0{}, ta[1], ra[1], [&](auto e) {
             if constexpr (e == 0) read_b(C0{}, sn);
             else read_a(C0{}, sn);
         });
-        block(C1{}, C0{}, tb[1], rb[1], top[3], [&](auto e) {
+        block(C1{}, C0{}, tb[1], rb[1], [&](auto e) {
             constexpr int h = PER_TILE / 2;
             static_for<h>([&](auto q) { copy_part(tt + ST, cur, std::integral_constant<int, e * h + decltype(q)::value>{}); });
         });
-        block(C0{}, C1{}, tb[0], rb[0], top[2], [&](auto e) {
+        block(C0{}, C1{}, tb[0], rb[0], [&](auto e) {
             if constexpr (e == 0) read_a(C1{}, sn);
         });
-        block(C1{}, C1{}, ta[0], ra[0], top[0], [&](auto e) {
+        block(C1{}, C1{}, ta[0], ra[0], [&](auto e) {
             if constexpr (e == 0) read_b(C1{}, sn);
         });
-        cur = next;
-        next = next + 1 == ST ? 0 : next + 1;
+        advance();
+        ++tt;
+        arrive();
+        fp32 = large();
+    } while (tt < nk && !fp32);
+    static_for<2>([&](auto i_) {
+        static_for<2>([&](auto j) { acc[i_][j] = (acc[i_][j] + low[i_][j]) * kF32xUnscale; });
+    });
+    // The rest of the wave's K steps from tile tt on in fp32 (v_mfma_f32_32x32x2_f32:
+    // lane half = K index, so instruction e takes values e and 8 + e of the step).
+    // The other waves keep their own pace: both loops meet the same barriers.
+    if (tt < nk) {
+        auto fp32_step = [&](const float (&xa)[2][8], const float (&xb)[2][8]) {
+            static_for<PER_TILE>([&](auto q) { copy_part(tt + ST, cur, q); });
+            static_for<8>([&](auto e) {
+                static_for<2>([&](auto i_) {
+                    static_for<2>([&](auto j) {
+                        acc[i_][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(xa[i_][e], xb[j][e], acc[i_][j], 0, 0, 0);
+                    });
+                });
+            });
+        };
+        fp32_step(ra, rb);
+        while (++tt < nk) {
+            advance();
+            float xa[2][8], xb[2][8];
+            const char* s = smem + cur * STAGE;
+            static_for<2>([&](auto b) {
+                OpA::read(xa[b], s, wm * 64 + b * 32, wk, lane);
+                OpB::read(xb[b], s + OpA::BYTES, wn * 64 + b * 32, wk, lane);
+            });
+            arrive();
+            fp32_step(xa, xb);
+        }
+        advance();
+        arrive();
     }
     vm_wait<0>();  // copies of tiles past the end still write (zeros) into LDS
-    bool bad = false;
-    static_for<4>([&](auto q) { bad |= top[q] >= kF32xLimit; });
-    const bool again = __syncthreads_or(bad ? 1 : 0) != 0;
-    if (!again) {
-        static_for<2>([&](auto i_) { static_for<2>([&](auto j) { acc[i_][j] = (acc[i_][j] + low[i_][j]) * kF32xUnscale; }); });
-        auto piece = [&](int k, auto c) { return reinterpret_cast<f32x4_t*>(smem + (k * NB + wb) * 16384 + c * 1024 + lane * 16); };
-        if (wk) {
+    __syncthreads();
+    auto piece = [&](int k, auto c) { return reinterpret_cast<f32x4_t*>(smem + (k * NB + wb) * 16384 + c * 1024 + lane * 16); };
+    if (wk) {
+        static_for<16>([&](auto c) {
+            constexpr int cc = decltype(c)::value;
+            const f32x16_t& v = acc[cc / 8][cc / 4 % 2];
+            *piece(wk - 1, c) = f32x4_t{v[4 * (cc % 4)], v[4 * (cc % 4) + 1], v[4 * (cc % 4) + 2], v[4 * (cc % 4) + 3]};
+        });
+    }
+    __syncthreads();
+    if (!wk) {
+        static_for<WK - 1>([&](auto k) {
             static_for<16>([&](auto c) {
                 constexpr int cc = decltype(c)::value;
-                const f32x16_t& v = acc[cc / 8][cc / 4 % 2];
-                *piece(wk - 1, c) = f32x4_t{v[4 * (cc % 4)], v[4 * (cc % 4) + 1], v[4 * (cc % 4) + 2], v[4 * (cc % 4) + 3]};
+                const f32x4_t p = *piece(k, c);
+                static_for<4>([&](auto e) { acc[cc / 8][cc / 4 % 2][4 * (cc % 4) + decltype(e)::value] += p[decltype(e)::value]; });
             });
-        }
-        __syncthreads();
-        if (!wk) {
-            static_for<WK - 1>([&](auto k) {
-                static_for<16>([&](auto c) {
-                    constexpr int cc = decltype(c)::value;
-                    const f32x4_t p = *piece(k, c);
-                    static_for<4>([&](auto e) { acc[cc / 8][cc / 4 % 2][4 * (cc % 4) + decltype(e)::value] += p[decltype(e)::value]; });
-                });
-            });
-        }
-    } else if (!wk) {
-        // The tile again in fp32 (v_mfma_f32_32x32x2_f32: lane half = K index), straight from memory.
-        static_for<2>([&](auto i_) {
-            static_for<2>([&](auto j) { static_for<16>([&](auto v) { acc[i_][j][decltype(v)::value] = 0.0f; }); });
         });
-        const int64_t am = m0 + wm * 64 + (lane & 31), bn = n0 + wn * 64 + (lane & 31);
-        for (int k0 = kbeg; k0 < kend; k0 += 2) {
-            const int64_t k = k0 + (lane >> 5);
-            float va[2], vb[2];
-            static_for<2>([&](auto b) {
-                const int64_t m = am + b * 32, n = bn + b * 32;
-                const uint32_t oa_ = (uint32_t)((TA ? k * a.lda + m : m * a.lda + k) * 4);
-                const uint32_t ob_ = (uint32_t)((TB ? n * a.ldb + k : k * a.ldb + n) * 4);
-                va[b] = __uint_as_float(buf_load4(oa.rs, k < kend && m < a.M ? oa_ : kOob));
-                vb[b] = __uint_as_float(buf_load4(ob.rs, k < kend && n < a.N ? ob_ : kOob));
-            });
-            static_for<2>([&](auto i_) {
-                static_for<2>([&](auto j) {
-                    acc[i_][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i_], vb[j], acc[i_][j], 0, 0, 0);
-                });
-            });
-        }
     }
     if (t.splits > 1) {
         uint64_t* const line = t.arrive + (size_t)tile * 8;

@@ -93,8 +93,8 @@ def test_fp32_unaligned_operands_run_on_terms(tb, off_a, off_b, M, N, K, monkeyp
     assert "ring kernel" in log or "fp32 split into bf16 terms" in log, log
 
 
-# Values that do not split into bf16 terms (infinities, NaNs, magnitudes from 2^28: the workgroups
-# that read them form their tiles in fp32), and rows and columns of tiny values.
+# Values that do not split into bf16 terms (infinities, NaNs, magnitudes from 2^28: the waves that
+# read them go on in fp32), and rows and columns of tiny values.
 @pytest.mark.parametrize("ring,rs", [(1, 1), (1, 3), (2, 1), (2, 4), (3, 2)])
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
 def test_f32x_range(ring, rs, ta, tb, monkeypatch):
@@ -154,6 +154,44 @@ def test_f32x_tiny_beside_ordinary(ring, rs, small, monkeypatch):
                       (isam.gemm(B.t().contiguous(), A.t().contiguous()), B.double().t().contiguous() @ A.double().t().contiguous(),
                        B.double().abs().t().contiguous() @ A.double().abs().t().contiguous())):
         assert bool(((C.double() - ref).abs() <= _tol(200) * S).all())
+
+
+# One large value (just split, the first that is not, and far out) in the first, a middle or the last
+# K tile of a slice: the waves that read it change to fp32 instructions there.
+@pytest.mark.parametrize("ring,rs", [(1, 1), (2, 2), (3, 1)])
+@pytest.mark.parametrize("k", [0, 15, 16, 70, 130, 235, 251])
+def test_f32x_large_values(ring, rs, k, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs={rs},skinny=0,small=0")
+    for v in (math.nextafter(2.0 ** 28, 0), 2.0 ** 28, -3e36):
+        A, B = _operands(132, 136, 252, 0, 0, 0, k)
+        A[5, k] = v
+        A[:, :k][A[:, :k].abs() < 0.1] = 0.0
+        _check(A, B, 0, 0)
+        _check(B.t().contiguous(), A.t().contiguous(), 0, 0)
+
+
+def test_f32x_large_values_cost_no_second_pass(monkeypatch):
+    # Large values everywhere in a column of A: the fp32 instructions run once, at about the speed of
+    # the fp32 tile kernel (measured: 1.2 times the time without; 6.5 times when the tiles were formed
+    # again).
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+
+    def best(A, B):
+        C, ms = isam.gemm(A, B, trans_b=True), []
+        for _ in range(8):
+            e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            e0.record()
+            for _ in range(10):
+                isam.gemm(A, B, C, trans_b=True)
+            e1.record()
+            torch.cuda.synchronize()
+            ms.append(e0.elapsed_time(e1))
+        return min(ms)
+
+    A, B = _operands(2048, 1024, 1024, 0, 1, 0, 3)
+    plain = best(A, B)
+    A[:, 0] = 1e30
+    assert best(A, B) <= 2.5 * plain
 
 
 # Streaming kernel on fp32 (N <= 256, K <= 128, B in registers): ragged last 32-row tile, K off the
