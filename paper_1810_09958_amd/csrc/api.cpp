@@ -644,7 +644,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                        const void* A, int64_t lda, const void* B, int64_t ldb, int accumulate,
                        int c_type, void* C, int64_t ldc, const float* bias, void* workspace,
                        size_t workspace_bytes, hipStream_t stream, const char* who, int64_t batch = 1,
-                       int64_t stride_a = 0, int64_t stride_b = 0, int64_t stride_c = 0) {
+                       int64_t stride_a = 0, int64_t stride_b = 0, int64_t stride_c = 0, bool split_copies = true) {
     // A strided batch is planned as one product of batch*M rows (for the tile
     // choice) and never split along K.
     GemmPlan p = batch > 1 ? plan_gemm(M * batch, N, K, ab_type, device_cus(), /*allow_skinny=*/false)
@@ -655,7 +655,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         p.sk = 0;
     }
     p.vec = (K == 0) ? 1 : (vec_ok(trans_a, trans_b, M, N, K, ab_type, A, lda, B, ldb) ? 1 : 0);
-    if (ab_type == kF32 && batch == 1 && K > 0) {
+    if (ab_type == kF32 && batch == 1 && K > 0 && split_copies) {
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         char* ws = static_cast<char*>(workspace);
         const size_t split_bytes = k.a_bytes + k.b_bytes;
@@ -880,8 +880,9 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
 
 size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Workspace of a product's preferred plan, as far as the sizes tell.
-size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type) {
+// Workspace of a product's preferred plan, as far as the sizes tell (split_copies:
+// as run_gemm's).
+size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, bool split_copies = true) {
     const int cus = device_cus();
     const GemmPlan p = plan_gemm(M, N, K, ab_type, cus);
     size_t ws = gemm_ws_bytes(p, M, N);
@@ -890,7 +891,7 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
     // them, and what the packed product then uses.
     const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
     const bool a_off = (trans_a ? M : K) % E != 0, b_off = (trans_b ? K : N) % E != 0;
-    if (ab_type == ISAM_F32) {
+    if (ab_type == ISAM_F32 && split_copies) {
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         if (k.pays) {
             // Split copies, or the kernel that forms the terms in registers and, as the
@@ -961,7 +962,7 @@ static size_t dwsep_ws(int64_t batch, int64_t Ho, int64_t Wo, int64_t C_in, int6
                        int64_t C_out, int in_type) {
     const int64_t M = batch * Ho * Wo, K = C_in * cm;
     const size_t y = align256((size_t)M * (size_t)K * dsize(in_type));
-    return y + gemm_query(0, 0, M, C_out, K, in_type);
+    return y + gemm_query(0, 0, M, C_out, K, in_type, /*split_copies=*/false);
 }
 
 // Which separable-convolution path runs: 1 = fused bf16 kernel, 2 = fused
@@ -1074,8 +1075,10 @@ isam_status_t isam_dwsep_conv(int64_t batch, int64_t H, int64_t W, int64_t C_in,
     if (e != hipSuccess) return hip_fail(e, who);
     char* gws = static_cast<char*>(workspace) + y_bytes;
     const size_t gws_bytes = workspace_bytes - y_bytes;
+    // Not on split copies, whose inputs have to be finite (and three times as large as
+    // Y): an infinite pixel makes infinite outputs here.
     return run_gemm(0, 0, Mp, C_out, Cm, in_type, workspace, Cm, pw_weight, C_out, 0, out_type, y, C_out,
-                    nullptr, gws_bytes ? gws : nullptr, gws_bytes, s, who);
+                    nullptr, gws_bytes ? gws : nullptr, gws_bytes, s, who, 1, 0, 0, 0, /*split_copies=*/false);
 }
 
 size_t isam_gru_forward_workspace_size(int64_t T, int64_t batch, int64_t input_size,

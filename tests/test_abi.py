@@ -147,6 +147,15 @@ def test_gemm_workspace_query_keeps_room_for_unaligned_fp32(L, monkeypatch):
         assert L.isam_gemm_workspace_size(0, tb, M, N, K, F32, F32) >= (M + N) * K * 4
 
 
+def test_dwsep_workspace_has_no_split_copies(L, monkeypatch):
+    # fp32 pointwise products never run on split copies of their operands: no room for them.
+    args = (6, 56, 56, 512, 1, 3, 3, 2, 1, 1024, F32, F32)
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    need = L.isam_dwsep_conv_workspace_size(*args)
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", "f32split=0")
+    assert need == L.isam_dwsep_conv_workspace_size(*args) < 2 * (6 * 28 * 28 * 512 * 4)
+
+
 def test_gemm_split_workspace_must_not_overlap_operands(L, monkeypatch):
     monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
     M, N, K = 4096, 4096, 4096
