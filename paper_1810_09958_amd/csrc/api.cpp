@@ -481,18 +481,19 @@ double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, b
 //   3072x1024x2048 TN 18.1 / 47.6, 2608x1032x4472 TN 37 / 77, 1024^3 NN 7.7 / 16.9,
 //   648x1520x3096 NT 20 / 28, 4968x128x2064 NN 12.3 / 22.5, 512x512x4096 NN 11.9 / 21.9.
 // ISAM_GEMM_CONFIG ring=0 switches it off, ring=1 / ring=2 force 128x128 / 64x64
-// tiles and rs=<n> the K slices; settings of the other kernels also switch it off.
+// tiles and rs=<n> the K slices; settings of the other kernels also switch it off;
+// rmix=1 (test hook) treats the slices of every tile as spread over several XCDs.
 //
 // fp32 products take the same tiles and K slices on the kernel of gemm_f32x.hpp
 // (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size, where that beats the
 // tile kernel's plan p.
 RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus,
                    bool may_split) {
-    RingPlan none{0, 1};
+    RingPlan none{0, 1, 0};
     if (M <= 0 || N <= 0 || K <= 0) return none;
     const bool f32 = ab_type == kF32;
     const int64_t nk = cdiv(K, 64);
-    int force = 0, force_s = 0;
+    int force = 0, force_s = 0, mixed = 0;
     if (const char* env = getenv("ISAM_GEMM_CONFIG")) {
         for (const char* k : {"tile=", "splits=", "dma=", "dmaw=", "sk=1", "stream=1", "ring=0"})
             if (strstr(env, k) && !(f32 && !strcmp(k, "ring=0"))) return none;
@@ -500,6 +501,7 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
         const char* q;
         if ((q = strstr(env, f32 ? "f32x=" : "ring="))) force = std::min(f32 ? 3 : 2, atoi(q + 5));
         if ((q = strstr(env, "rs="))) force_s = atoi(q + 3);
+        mixed = strstr(env, "rmix=1") ? 1 : 0;
     }
     // What the fp32 kernel has to beat (operands off 16 bytes are copied first: a launch
     // and about 3 TB/s).
@@ -522,7 +524,7 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
                                         : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
                                               (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);
             if (!best.ring || us < best_us) {
-                best = RingPlan{ring, (int)sp};
+                best = RingPlan{ring, (int)sp, mixed};
                 best_us = us;
             }
         }
@@ -692,7 +694,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
         const bool special = special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
                                             !((uintptr_t)A & 15) && lda * es % 16 == 0, cus);
-        RingPlan r = special ? RingPlan{0, 1} : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
+        RingPlan r = special ? RingPlan{0, 1, 0} : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
         if (r.ring) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, need_a, need_b);
             const size_t pack_bytes = k.a_bytes + k.b_bytes;

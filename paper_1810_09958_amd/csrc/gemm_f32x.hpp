@@ -332,16 +332,39 @@ __global__ __launch_bounds__(64 * WM * WN * WK, OCC) void gemm_f32x_kernel(GemmA
         __syncthreads();  // every wave's partial sums are in L2
         int* word = reinterpret_cast<int*>(smem);
         if (tid == 0) {
-            bool mixed = false;
+            bool mixed = t.mixed != 0;
             const bool last = ring_arrive(line, old, t.epoch, t.splits, &mixed);
             *word = (last ? 1 : 0) | (mixed ? 2 : 0);
         }
         __syncthreads();
         const int state = __builtin_amdgcn_readfirstlane(*word);
         if (!(state & 1) || wk) return;
-        ring_sum<2, 2, BM * BN * 4>(acc, make_rsrc(reinterpret_cast<char*>(a.partial) + (size_t)tile * t.splits * (BM * BN * 4),
-                                                   (uint32_t)(t.splits * (BM * BN * 4))), t.splits, wb, lane);
-        if (state & 2) acc_fill_nan<2, 2>(acc);  // slices on several XCDs: see gemm_ring.hpp
+        if (!(state & 2)) {
+            ring_sum<2, 2, BM * BN * 4>(acc, make_rsrc(reinterpret_cast<char*>(a.partial) + (size_t)tile * t.splits * (BM * BN * 4),
+                                                       (uint32_t)(t.splits * (BM * BN * 4))), t.splits, wb, lane);
+        } else {
+            // Slices on several XCDs (see gemm_ring.hpp): all of K here, from memory, in fp32.
+            static_for<2>([&](auto i_) {
+                static_for<2>([&](auto j) { static_for<16>([&](auto v) { acc[i_][j][decltype(v)::value] = 0.0f; }); });
+            });
+            const int64_t am = m0 + wm * 64 + (lane & 31), bn = n0 + wn * 64 + (lane & 31);
+            for (int k0 = 0; k0 < (int)a.K; k0 += 2) {
+                const int64_t k = k0 + (lane >> 5);
+                float va[2], vb[2];
+                static_for<2>([&](auto b) {
+                    const int64_t m = am + b * 32, n = bn + b * 32;
+                    const uint32_t oa_ = (uint32_t)((TA ? k * a.lda + m : m * a.lda + k) * 4);
+                    const uint32_t ob_ = (uint32_t)((TB ? n * a.ldb + k : k * a.ldb + n) * 4);
+                    va[b] = __uint_as_float(buf_load4(oa.rs, k < a.K && m < a.M ? oa_ : kOob));
+                    vb[b] = __uint_as_float(buf_load4(ob.rs, k < a.K && n < a.N ? ob_ : kOob));
+                });
+                static_for<2>([&](auto i_) {
+                    static_for<2>([&](auto j) {
+                        acc[i_][j] = __builtin_amdgcn_mfma_f32_32x32x2f32(va[i_], vb[j], acc[i_][j], 0, 0, 0);
+                    });
+                });
+            }
+        }
     }
     if (wk) return;
     // staging past the K steps' sums, which slower waves may still be reading

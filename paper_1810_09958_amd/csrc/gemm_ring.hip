@@ -34,6 +34,7 @@ hipError_t ring_args(const GemmArgs& a, const RingPlan& r, const RingPadded& pad
     t.tiles_m = (int)((a.M + bm - 1) / bm);
     t.tiles_n = (int)((a.N + bn - 1) / bn);
     t.group_m = 8;
+    t.mixed = r.mixed;
     t.xcds = cus % 32 == 0 ? cus / 32 : 1;
     const int64_t tiles = (int64_t)t.tiles_m * t.tiles_n;
     t.per_xcd = (int)((tiles + t.xcds - 1) / t.xcds);

@@ -18,7 +18,9 @@
 //     xcds); each leaves its fp32 partial sums in the workspace, in that XCD's
 //     L2, and counts itself in; the last to arrive adds the S partial sums in
 //     slice order (the same sum whoever is last) and writes C.  Nobody waits,
-//     so the form needs no co-residency and no second kernel.
+//     so the form needs no co-residency and no second kernel; the counting word
+//     also collects the XCDs, and slices that ran on several (a stream with a CU
+//     mask, another partition) make the last arrival form the tile by itself.
 // Measured per call, back to back, against the plans it replaces (register-
 // staged 128x64 / 64x64 tiles, a transposing copy of A, split-K with a
 // reduction kernel): 3072x1024x2048 TN accumulating 47.7 -> 22.1 us,
@@ -41,6 +43,7 @@ struct RingArgs {
     int xcds, per_xcd;     // tiles per XCD (the last XCDs' ranges may be short or empty)
     int splits;            // K slices per tile
     int k_per_split;       // multiple of 64
+    int mixed;             // 1: treat every tile's slices as spread over XCDs (test hook)
     uint32_t a_bytes, b_bytes;  // extents of A and B (per problem of a batch)
     uint64_t epoch;        // arrival words of this launch: epoch (not 0) in the upper 40 bits
     uint64_t* arrive;      // one 64-byte line per tile
@@ -95,6 +98,16 @@ struct RingOperand {
         const uint32_t off = kq[Q] + k0 < kend ? base[Q] + (uint32_t)k0 * kstep : kOob;
         dma16(rs, __builtin_amdgcn_readfirstlane(lds + (uint32_t)((wid * INSTR + Q) * 1024)), off);
     }
+    // The lane's 8 K values from k of row r, from memory (rows and K values outside: zeros).
+    __device__ __forceinline__ static uint4 direct(__amdgpu_buffer_rsrc_t rs, int64_t ld, int64_t rows, int64_t K, int64_t r, int k) {
+        if constexpr (KC) {
+            return buf_load16(rs, r < rows && k < K ? (uint32_t)((r * ld + k) * 2) : kOob);
+        } else {
+            uint32_t h[8];
+            static_for<8>([&](auto e) { h[e] = buf_load2(rs, r < rows && k + e < K ? (uint32_t)(((k + e) * ld + r) * 2) : kOob) & 0xffffu; });
+            return make_uint4(h[0] | h[1] << 16, h[2] | h[3] << 16, h[4] | h[5] << 16, h[6] | h[7] << 16);
+        }
+    }
     // MFMA operand block (32 rows from r0, K step ks) of the stage at s.
     __device__ __forceinline__ static uint4 frag(const char* s, int r0, int ks, int lane) {
         if constexpr (KC) {
@@ -118,7 +131,8 @@ struct RingOperand {
 // The word holds epoch (40 bits), the XCDs seen (one bit each, 16 bits) and
 // the count (8 bits); whatever an earlier launch or another program left there
 // differs in the epoch and counts as zero.  The last arrival clears the word, so
-// a captured launch (the same epoch on every replay) starts from zero too.  *mixed: slices ran on several XCDs.
+// a captured launch (the same epoch on every replay) starts from zero too.  Sets
+// *mixed if slices ran on several XCDs.
 // `old`: a recent reading of the word (a stale one costs another round trip).
 __device__ __forceinline__ bool ring_arrive(uint64_t* word, uint64_t old, uint64_t epoch, int splits, bool* mixed) {
     const unsigned xcc = __builtin_amdgcn_s_getreg((20) | (0 << 6) | (31 << 11)) & 0xfu;  // HW_REG_XCC_ID
@@ -129,7 +143,7 @@ __device__ __forceinline__ bool ring_arrive(uint64_t* word, uint64_t old, uint64
         if (__hip_atomic_compare_exchange_strong(word, &old, next, __ATOMIC_RELAXED, __ATOMIC_RELAXED,
                                                  __HIP_MEMORY_SCOPE_AGENT)) {
             const uint64_t seen = (next >> 8) & 0xffff;
-            *mixed = (seen & (seen - 1)) != 0;
+            if (seen & (seen - 1)) *mixed = true;
             const bool last = (int)(next & 0xff) == splits;
             if (last) __hip_atomic_store(word, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
             return last;
@@ -277,7 +291,7 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmArgs a
         __syncthreads();  // every wave's partial sums are in L2
         int* word = reinterpret_cast<int*>(smem);
         if (tid == 0) {
-            bool mixed = false;
+            bool mixed = t.mixed != 0;
             const bool last = ring_arrive(line, old, t.epoch, t.splits, &mixed);
             *word = (last ? 1 : 0) | (mixed ? 2 : 0);
         }
@@ -285,11 +299,25 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmArgs a
         const int state = __builtin_amdgcn_readfirstlane(*word);
         if (!(state & 1)) return;
         __syncthreads();
-        ring_sum<MI, NI, BM * BN * 4>(acc, make_rsrc(reinterpret_cast<char*>(a.partial) + (size_t)tile * t.splits * (BM * BN * 4),
-                                                          (uint32_t)(t.splits * (BM * BN * 4))), t.splits, wid, lane);
-        // Slices on several XCDs (never seen: workgroups are dealt in turn)
-        // could not have read each other's sums.
-        if (state & 2) acc_fill_nan<MI, NI>(acc);
+        if (!(state & 2)) {
+            ring_sum<MI, NI, BM * BN * 4>(acc, make_rsrc(reinterpret_cast<char*>(a.partial) + (size_t)tile * t.splits * (BM * BN * 4),
+                                                              (uint32_t)(t.splits * (BM * BN * 4))), t.splits, wid, lane);
+        } else {
+            // Slices on several XCDs (workgroups are dealt to them in turn, so never
+            // seen) cannot read each other's sums, which are in their own L2: all of K
+            // here, straight from memory (the way above in a loop cost every product
+            // 2 %).
+            static_for<MI>([&](auto i_) {
+                static_for<NI>([&](auto j) { static_for<16>([&](auto v) { acc[i_][j][decltype(v)::value] = 0.0f; }); });
+            });
+            for (int k0 = 0; k0 < (int)a.K; k0 += 16) {
+                const int k = k0 + (lane >> 5) * 8;
+                uint4 fa[MI], fb[NI];
+                static_for<MI>([&](auto i_) { fa[i_] = OpA::direct(oa.rs, a.lda, a.M, a.K, m0 + wm * WTM + i_ * 32 + (lane & 31), k); });
+                static_for<NI>([&](auto j) { fb[j] = OpB::direct(ob.rs, a.ldb, a.N, a.K, n0 + wn * WTN + j * 32 + (lane & 31), k); });
+                static_for<MI>([&](auto i_) { static_for<NI>([&](auto j) { mfma32_bf16(acc[i_][j], fa[i_], fb[j]); }); });
+            }
+        }
     }
     store_acc_tile<MI, NI, WTM, WTN, NW, true>(a, acc, smem, m0, n0, wm, wn, wid, lane);
 }

@@ -72,6 +72,7 @@ bool gemm_sk_tile(int tile);
 // slices per tile, summed in the kernel through the workspace (a.partial).
 struct RingPlan {
     int ring, splits;
+    int mixed;  // 1: treat every tile's slices as spread over XCDs (test hook)
 };
 // Rows are readable to ld values each (operands packed by the library): the
 // last row's 16-byte pieces may then pass the row's last value.

@@ -55,6 +55,18 @@ def test_f32x_forced(ring, ta, tb, M, N, K, rs, monkeypatch):
     _check(*_operands(M, N, K, ta, tb, 4, N + K), ta, tb, acc=True, ct=torch.bfloat16)
 
 
+# Slices that ran on several XCDs (forced from the host): the last arrival forms the whole tile, with
+# and without values that take the fp32 instructions.
+@pytest.mark.parametrize("ring", [1, 2, 3])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0)])
+def test_f32x_slices_on_several_xcds(ring, ta, tb, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"f32x={ring},rs=3,rmix=1,skinny=0,small=0")
+    A, B = _operands(260, 200, 652, ta, tb, 4, ring)
+    _check(A, B, ta, tb, acc=True)
+    (A.t() if ta else A)[7, 300] = math.inf
+    _check(A, B, ta, tb)
+
+
 # As planned: aligned and odd sizes (operands copied into padded rows), with too little
 # workspace for slices or copies, and the strided batch of a convolution.
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])

@@ -56,6 +56,16 @@ def test_ring_forced(ring, ta, tb, M, N, K, rs, monkeypatch):
     _check(M, N, K, ta, tb, ct="bf16", acc=True, pad=8, seed=M + N + rs)
 
 
+# Slices that ran on several XCDs (forced from the host): the last arrival forms the whole tile.
+@pytest.mark.parametrize("ring", ["1", "2"])
+@pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
+@pytest.mark.parametrize("M,N,K,rs", [(136, 120, 648, 3), (264, 72, 2000, 7), (128, 128, 128, 2)])
+def test_ring_slices_on_several_xcds(ring, ta, tb, M, N, K, rs, monkeypatch):
+    monkeypatch.setenv("ISAM_GEMM_CONFIG", f"ring={ring},rs={rs},rmix=1,skinny=0,small=0")
+    _check(M, N, K, ta, tb, seed=M + K + rs)
+    _check(M, N, K, ta, tb, ct="bf16", acc=True, pad=8, seed=M + N + rs)
+
+
 # Odd sizes: operands copied into padded rows, C rows that are not 16-byte aligned.
 @pytest.mark.parametrize("ta,tb", [(0, 0), (0, 1), (1, 0), (1, 1)])
 @pytest.mark.parametrize("M,N,K", [(1000, 1537, 1023), (89, 170, 800), (131, 67, 1573), (700, 12, 312), (65, 71, 100)])
