@@ -43,6 +43,7 @@ struct RingArgs {
     int xcds, per_xcd;     // tiles per XCD (the last XCDs' ranges may be short or empty)
     int splits;            // K slices per tile
     int k_per_split;       // multiple of 64
+    int fold;              // K tiles (even) whose products are summed before they join the total
     int mixed;             // 1: treat every tile's slices as spread over XCDs (test hook)
     uint32_t a_bytes, b_bytes;  // extents of A and B (per problem of a batch)
     uint64_t epoch;        // arrival words of this launch: epoch (not 0) in the upper 40 bits
@@ -215,16 +216,30 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmArgs a
     const uint32_t sbase = lds_addr_of(smem);
 
     // A wave of one 32x32 block has a second accumulator for odd 16-deep K steps:
-    // half as many additions one after the other, in time and in the sum's error
-    // (1024^3, fp32 out: 1.3e-7 of the norm, 1.8e-7 on the tile kernel; two sets of
-    // the 128x128 tile's accumulators would spill).
+    // half as many additions one after the other.  Every t.fold K tiles the accumulators
+    // join a total and start from zero, so a slice of n K tiles is summed in two
+    // short chains (about 2 sqrt(n) additions each for 128x128) instead of one of
+    // 4 n, whose error grows with the root of its length.  Error of the norm, fp32
+    // out (one chain / the plan replaced, up to eight slices / two chains), and us:
+    // 2608x1032x4472 TN 4.2e-7 / 1.8e-7 / 1.3e-7, 41.5 / 81 / 41.9; 1024x2048x8192
+    // 4.0e-7 / 1.9e-7 / 1.2e-7, 48.6 / 53 / 49.5; 1024^3 1.3e-7 / 1.8e-7 / 7.7e-8, 9.0 /
+    // 15.7 / 9.0.  The folds stand between loops and not in one under a condition, which cost
+    // 10 to 35 %.
     constexpr int ODD = MI * NI == 1 ? 1 : 0;
-    f32x16_t acc[MI][NI], odd[MI][NI];
-    static_for<MI>([&](auto i_) {
-        static_for<NI>([&](auto j) {
-            static_for<16>([&](auto v) { acc[i_][j][decltype(v)::value] = odd[i_][j][decltype(v)::value] = 0.0f; });
+    f32x16_t acc[MI][NI], odd[MI][NI], total[MI][NI];
+    auto each = [&](auto&& f) {
+        static_for<MI>([&](auto i_) { static_for<NI>([&](auto j) { f(total[i_][j], acc[i_][j], odd[i_][j]); }); });
+    };
+    auto zero = [](f32x16_t& x) { static_for<16>([&](auto v) { x[decltype(v)::value] = 0.0f; }); };
+    auto fold = [&] {
+        each([&](f32x16_t& s, f32x16_t& x, f32x16_t& y) {
+            if constexpr (ODD) x += y;
+            s += x;
+            zero(x);
+            zero(y);
         });
-    });
+    };
+    each([&](f32x16_t& s, f32x16_t& x, f32x16_t& y) { zero(s); zero(x); zero(y); });
 
     // Tiles past the end are copied too (every offset out of range: zeros, no
     // memory read), so the number of copies in flight is the same in each step.
@@ -275,13 +290,19 @@ __global__ __launch_bounds__(64 * WM * WN, OCC) void gemm_ring_kernel(GemmArgs a
     vm_wait<(ST - 1) * PER_TILE>();
     block_sync();
     static_for<READS>([&](auto r) { read_part(f0, smem, r); });
-    for (int tt = 0; tt < nk; tt += 2) {
-        step(f0, f1, tt);
-        if (tt + 1 >= nk) break;
-        step(f1, f0, tt + 1);
+    int tt = 0;
+    for (const int even = nk & ~1;;) {
+        for (const int stop = min(even, tt + t.fold); tt < stop; tt += 2) {
+            step(f0, f1, tt);
+            step(f1, f0, tt + 1);
+        }
+        if (tt >= even) break;
+        fold();
     }
+    if (nk & 1) step(f0, f1, tt);
     vm_wait<0>();  // copies of tiles past the end still write (zeros) into LDS
-    if constexpr (ODD) acc[0][0] += odd[0][0];
+    fold();
+    each([](f32x16_t& s, f32x16_t& x, f32x16_t&) { x = s; });
     __syncthreads();
     if (t.splits > 1) {
         uint64_t* const line = t.arrive + (size_t)tile * 8;

@@ -84,6 +84,24 @@ def test_ring_unaligned_operands(ta, tb, room, monkeypatch):
     _check(520, 648, 1032, ta, tb, pad=3, shift=1, seed=5, workspace=ws)
 
 
+# Against 64 bits, no larger an error than the plans the kernel stands in for, which cut deep K into
+# up to eight slices: K from one fold of the accumulators to many, an odd number of K tiles, and a
+# short last one.
+@pytest.mark.parametrize("M,N,K,ta,tb", [(2608, 1032, 4472, 1, 0), (2048, 1024, 4096, 0, 1), (1024, 2048, 8192, 0, 0),
+                                         (512, 512, 16384, 0, 0), (64, 960, 1024, 1, 0), (568, 208, 936, 1, 0),
+                                         (144, 3864, 4152, 0, 0)])
+def test_ring_error_is_no_larger_than_with_more_slices(M, N, K, ta, tb, monkeypatch):
+    g = torch.Generator(device="cuda").manual_seed(K)
+    A = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
+    B = torch.randn((N, K) if tb else (K, N), device="cuda", generator=g).bfloat16()
+    ref = (A.t() if ta else A).double().contiguous() @ (B.t() if tb else B).double().contiguous()
+    err = {}
+    for env in ("", "ring=0"):
+        monkeypatch.setenv("ISAM_GEMM_CONFIG", env)
+        err[env] = float((isam.gemm(A, B, trans_a=bool(ta), trans_b=bool(tb)).double() - ref).norm() / ref.norm())
+    assert err[""] <= err["ring=0"], err
+
+
 def test_ring_deterministic_and_captured(monkeypatch):
     # K slices summed by whichever workgroup arrives last: the same bits every time, on a
     # workspace that holds anything, and when one captured launch is replayed.
