@@ -486,9 +486,10 @@ double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, b
 //
 // fp32 products take the same tiles and K slices on the kernel of gemm_f32x.hpp
 // (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size, where that beats the
-// tile kernel's plan p.
+// tile kernel's plan p.  room: workspace bytes that may hold the slices' sums (as many
+// slices as fit; 0: none).
 RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus,
-                   bool may_split) {
+                   size_t room) {
     RingPlan none{0, 1, 0};
     if (M <= 0 || N <= 0 || K <= 0) return none;
     const bool f32 = ab_type == kF32;
@@ -516,7 +517,8 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
         int bm, bn;
         gemm_ring_dims(ring, &bm, &bn);
         const int64_t tiles = batch * cdiv(M, bm) * cdiv(N, bn);
-        const int64_t most = may_split ? std::max<int64_t>(1, std::min<int64_t>(force ? 255 : 8, nk / (force ? 1 : 4))) : 1;
+        int64_t most = room ? std::max<int64_t>(1, std::min<int64_t>(force ? 255 : 8, nk / (force ? 1 : 4))) : 1;
+        while (most > 1 && gemm_ring_ws_bytes(RingPlan{ring, (int)most, 0}, M, N) > room) --most;
         for (int64_t sp = 1; sp <= most; ++sp) {
             if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
             const int64_t iters = cdiv(nk, sp), wgs = tiles * cdiv(nk, iters), per_cu = cdiv(wgs, cus);
@@ -594,16 +596,30 @@ bool special_kernel(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int6
     return vec && !trans_a && !trans_b && stream_pays(M, N, K, ab_type, cus);
 }
 
+// The part of a workspace behind `used` bytes that may hold K slices' sums: from the
+// next multiple of 256 bytes (a caller's workspace may start anywhere).
+constexpr size_t kAnyRoom = SIZE_MAX / 2;
+size_t slice_offset(const void* ws, size_t used) {
+    const uintptr_t at = (uintptr_t)ws + used;
+    return used + (size_t)(((at + 255) & ~(uintptr_t)255) - at);
+}
+size_t slice_room(const void* ws, size_t bytes, size_t used) {
+    const size_t at = slice_offset(ws, used);
+    return ws && bytes > at ? bytes - at : 0;
+}
+
 // Whether a product that could run on split copies of its operands (split_plan) takes
 // the kernel that forms the terms in registers instead: small grids where its plan
-// pays, with operands that are aligned or can be copied into `room` bytes of
-// workspace.  Otherwise the split copies keep it, which take any alignment.
+// pays, with operands that are aligned or can be copied into the workspace.
+// Otherwise the split copies keep it, which take any alignment.
 bool f32x_over_split(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a,
-                     bool need_b, size_t room, int cus) {
-    if (!f32x_grid(M, N, cus) || !plan_ring(p, M, N, K, kF32, !need_a && !need_b, 1, cus, true).ring) return false;
-    if (!need_a && !need_b) return true;
+                     bool need_b, const void* ws, size_t bytes, int cus) {
+    if (!f32x_grid(M, N, cus)) return false;
     const RingPack k = ring_pack(trans_a, trans_b, M, N, K, kF32, need_a, need_b);
-    return k.a_bytes + k.b_bytes <= room && ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k);
+    const size_t copies = k.a_bytes + k.b_bytes;
+    if (copies && (copies > bytes || !ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k))) return false;
+    const size_t room = bytes == kAnyRoom ? kAnyRoom : slice_room(ws, bytes, copies);
+    return plan_ring(p, M, N, K, kF32, !need_a && !need_b, 1, cus, room).ring != 0;
 }
 
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
@@ -663,7 +679,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const size_t split_bytes = k.a_bytes + k.b_bytes;
         if (k.pays && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes &&
             !f32x_over_split(p, trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
-                             pack_b_needed(trans_b, N, K, ab_type, B, ldb), workspace_bytes, device_cus())) {
+                             pack_b_needed(trans_b, N, K, ab_type, B, ldb), ws, workspace_bytes, device_cus())) {
             const int64_t es = (int64_t)dsize(ab_type);
             const size_t a_b = (size_t)(((M - 1) * lda + K) * es);
             const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
@@ -694,18 +710,19 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         const bool need_a = pack_a_needed(trans_a, M, K, ab_type, A, lda), need_b = pack_b_needed(trans_b, N, K, ab_type, B, ldb);
         const bool special = special_kernel(p, trans_a, trans_b, M, N, K, ab_type, p.vec && batch == 1,
                                             !((uintptr_t)A & 15) && lda * es % 16 == 0, cus);
-        RingPlan r = special ? RingPlan{0, 1, 0} : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, batch == 1);
-        if (r.ring) {
+        if (!special) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, need_a, need_b);
             const size_t pack_bytes = k.a_bytes + k.b_bytes;
             char* ws = static_cast<char*>(workspace);
-            const bool ws_ok = ws && ((uintptr_t)ws & 255) == 0 && batch == 1;
             const bool packs = pack_bytes > 0;
-            const bool fits = !packs || (ws_ok && workspace_bytes >= pack_bytes && ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k));
-            if (fits && r.splits > 1 && (!ws_ok || workspace_bytes < pack_bytes + gemm_ring_ws_bytes(r, M, N)))
-                r = plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus, false);
-            if (fits && r.ring) {
-                const size_t used = pack_bytes + gemm_ring_ws_bytes(r, M, N);
+            const bool fits = !packs || (batch == 1 && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= pack_bytes &&
+                                         ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k));
+            const RingPlan r = !fits ? RingPlan{0, 1, 0}
+                                     : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus,
+                                                 batch == 1 ? slice_room(ws, workspace_bytes, pack_bytes) : 0);
+            if (r.ring) {
+                const size_t sums = gemm_ring_ws_bytes(r, M, N), sums_at = slice_offset(ws, pack_bytes);
+                const size_t used = sums ? sums_at + sums : pack_bytes;
                 if (used) {
                     const size_t a_b = (size_t)((trans_a ? (K - 1) * lda + M : (M - 1) * lda + K) * es);
                     const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
@@ -721,7 +738,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                 a.A = k.a ? ws : A;
                 a.B = k.b ? ws + k.a_bytes : B;
                 a.C = C;
-                a.partial = reinterpret_cast<float*>(ws ? ws + pack_bytes : nullptr);
+                a.partial = reinterpret_cast<float*>(sums ? ws + sums_at : nullptr);
                 a.bias = bias;
                 a.M = M;
                 a.N = N;
@@ -888,6 +905,11 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
     const int cus = device_cus();
     const GemmPlan p = plan_gemm(M, N, K, ab_type, cus);
     size_t ws = gemm_ws_bytes(p, M, N);
+    // K slices' sums, wherever the caller's workspace starts
+    auto sums = [&](const RingPlan& r) {
+        const size_t n = gemm_ring_ws_bytes(r, M, N);
+        return n ? n + 255 : 0;
+    };
     // Rows that the sizes alone make unfit for 16-byte copies (a contiguous
     // dimension off the vector width), and bf16 A given as [K][M]: room to pack
     // them, and what the packed product then uses.
@@ -899,21 +921,20 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
             // Split copies, or the kernel that forms the terms in registers and, as the
             // split copies take operands of any alignment, room for copies of both.
             const RingPack both = ring_pack(trans_a, trans_b, M, N, K, kF32, true, true);
-            const size_t copies = both.a_bytes + both.b_bytes;
-            if (!f32x_over_split(p, trans_a, trans_b, M, N, K, a_off, b_off, copies, cus) ||
-                !f32x_over_split(p, trans_a, trans_b, M, N, K, true, true, copies, cus))
+            if (!f32x_over_split(p, trans_a, trans_b, M, N, K, a_off, b_off, nullptr, kAnyRoom, cus) ||
+                !f32x_over_split(p, trans_a, trans_b, M, N, K, true, true, nullptr, kAnyRoom, cus))
                 ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
             else
-                ws = std::max(ws, copies + gemm_ring_ws_bytes(plan_ring(p, M, N, K, kF32, false, 1, cus, true), M, N));
+                ws = std::max(ws, both.a_bytes + both.b_bytes + sums(plan_ring(p, M, N, K, kF32, false, 1, cus, kAnyRoom)));
             if (!f32x_grid(M, N, cus)) return ws;
         }
     }
     {
-        const RingPlan r = plan_ring(p, M, N, K, ab_type, !a_off && !b_off, 1, cus, true);
+        const RingPlan r = plan_ring(p, M, N, K, ab_type, !a_off && !b_off, 1, cus, kAnyRoom);
         if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, !a_off && !b_off, K % E == 0, cus)) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, a_off, b_off);
             if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k))
-                ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ring_ws_bytes(r, M, N));
+                ws = std::max(ws, k.a_bytes + k.b_bytes + sums(r));
         }
     }
     const bool a_mis = a_off || (trans_a && ab_type == ISAM_BF16);

@@ -102,6 +102,23 @@ def test_ring_error_is_no_larger_than_with_more_slices(M, N, K, ta, tb, monkeypa
     assert err[""] <= err["ring=0"], err
 
 
+# A workspace of the queried size that starts anywhere has room for the planned K slices, and one of
+# half the size for fewer; nothing outside it is written.
+@pytest.mark.parametrize("off", [0, 2, 16, 100, 255])
+def test_ring_workspace_at_any_address(off, monkeypatch, capfd):
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    monkeypatch.setenv("ISAM_LOG", "1")
+    M, N, K = 512, 512, 4096
+    slices = {}
+    for part in (1, 2):
+        need = isam.gemm_workspace_size(M, N, K, 1, 0) if part == 1 else 64 * (2 * 64 * 64 * 4 + 64) + 255
+        buf = torch.full((off + need + 512,), 0xA5, device="cuda", dtype=torch.uint8)
+        _check(M, N, K, 0, 0, workspace=buf[off : off + need])
+        slices[part] = int(capfd.readouterr().err.split(" K slices")[0].split()[-1])
+        assert bool((buf[:off] == 0xA5).all()) and bool((buf[off + need :] == 0xA5).all())
+    assert slices == {1: 4, 2: 2}
+
+
 def test_ring_deterministic_and_captured(monkeypatch):
     # K slices summed by whichever workgroup arrives last: the same bits every time, on a
     # workspace that holds anything, and when one captured launch is replayed.
