@@ -20,6 +20,7 @@
 #include "kernels.hpp"
 
 #include <algorithm>
+#include <cstdio>
 #include <cstdlib>
 
 namespace isam {
@@ -357,8 +358,10 @@ __global__ __launch_bounds__(kDwLdsThreads) void dw3x3_lds_kernel(DwArgs a, int 
 }
 
 // KxK stencil of stride S, any padding, depth multiplier 1, whole 16-byte
-// channel vectors (down-sampling 3x3 and the 5x5 layers).  Bound: HBM, one read
-// of X and one write of Y.  A thread owns one channel vector of one output
+// channel vectors (down-sampling 3x3 and the 5x5 layers).  Bound: HBM for 3x3, one read
+// of X and one write of Y; vector instructions for 5x5, above all in bf16, where each
+// vector of a row and of the taps is unpacked again for every use (and 37 to 61 registers
+// spill).  A thread owns one channel vector of one output
 // column over R output rows and walks the (R-1) S + K input rows they need once,
 // each row feeding every output row whose window holds it, so the loads of a
 // thread do not depend on each other and neighbouring columns and rows meet in
@@ -376,7 +379,7 @@ __global__ __launch_bounds__(kDwLdsThreads) void dw3x3_lds_kernel(DwArgs a, int 
 // 16x56x56x128 -> 128 fp32; four spill).
 __host__ __device__ constexpr int dw_rows(int k) { return k == 3 ? 1 : 2; }
 
-template <typename T, typename TY, int K, int S>
+template <typename T, int K, int S>
 __global__ __launch_bounds__(256, K == 3 ? 4 : 2) void dw_window_kernel(DwArgs a) {
     constexpr int E = 16 / (int)sizeof(T), R = dw_rows(K), ROWS = (R - 1) * S + K;
     const uint32_t CV = (uint32_t)(a.C / E), Wo = (uint32_t)a.Wo, nseg = (uint32_t)((a.Ho + R - 1) / R);
@@ -442,17 +445,17 @@ __global__ __launch_bounds__(256, K == 3 ? 4 : 2) void dw_window_kernel(DwArgs a
     const bool inside = y0 >= 0 && y0 + ROWS <= a.H && x0 >= 0 && x0 + K <= a.W;
     if (__builtin_amdgcn_ballot_w64(!inside) == 0) walk(std::false_type{});
     else walk(std::true_type{});
-    TY* yp = static_cast<TY*>(a.y) + ((b * a.Ho + i0) * a.Wo + j) * a.C + c0;
+    T* yp = static_cast<T*>(a.y) + ((b * a.Ho + i0) * a.Wo + j) * a.C + c0;
 #pragma unroll
     for (int r = 0; r < R; ++r)
-        if (i0 + r < a.Ho) dw_store<T, TY>(yp + (int64_t)r * a.Wo * a.C, acc[r]);
+        if (i0 + r < a.Ho) dw_store<T, T>(yp + (int64_t)r * a.Wo * a.C, acc[r]);
 }
 
-template <typename T, typename TY>
+template <typename T>
 void (*dw_window_fn(int64_t k, int64_t stride))(DwArgs) {
-    if (k == 3 && stride == 2) return dw_window_kernel<T, TY, 3, 2>;
-    if (k == 5 && stride == 1) return dw_window_kernel<T, TY, 5, 1>;
-    if (k == 5 && stride == 2) return dw_window_kernel<T, TY, 5, 2>;
+    if (k == 3 && stride == 2) return dw_window_kernel<T, 3, 2>;
+    if (k == 5 && stride == 1) return dw_window_kernel<T, 5, 1>;
+    if (k == 5 && stride == 2) return dw_window_kernel<T, 5, 2>;
     return nullptr;
 }
 
@@ -543,18 +546,16 @@ hipError_t launch_depthwise(const DwArgs& a, hipStream_t s) {
             else hipLaunchKernelGGL((dw3x3_s1_kernel<float, float>), grid, block, 0, s, a);
         }
     } else {
-        // 3x3 stride 2 and 5x5 on whole channel vectors: the window kernel.
-        if (vecs && a.kh == a.kw) {
+        // 3x3 stride 2 and 5x5 on whole channel vectors, Y in X's type: the window kernel.
+        if (vecs && a.kh == a.kw && a.y_type == a.in_type) {
             const int rows = dw_rows((int)a.kh);
-            void (*fn)(DwArgs) =
-                a.in_type == kBF16
-                    ? (a.y_type == kBF16 ? dw_window_fn<bf16_t, bf16_t>(a.kh, a.stride) : dw_window_fn<bf16_t, float>(a.kh, a.stride))
-                    : (a.y_type == kBF16 ? dw_window_fn<float, bf16_t>(a.kh, a.stride) : dw_window_fn<float, float>(a.kh, a.stride));
+            void (*fn)(DwArgs) = a.in_type == kBF16 ? dw_window_fn<bf16_t>(a.kh, a.stride) : dw_window_fn<float>(a.kh, a.stride);
             const int64_t nt = a.batch * ((a.Ho + rows - 1) / rows) * a.Wo * (a.C / E);
             const int64_t nb = ((nt + 255) / 256 + 7) / 8 * 8;  // a multiple of the XCD count
             // Below 128 workgroups a 5x5 thread's 30 loads are one after the other on an
             // idle chip; the generic kernel's one value per thread is as fast there.
             if (fn && nb * 256 < (int64_t(1) << 31) && (a.kh == 3 || nb >= 128)) {
+                if (const char* v = getenv("ISAM_LOG"); v && v[0] && v[0] != '0') fprintf(stderr, "[isam] depthwise window kernel\n");
                 hipLaunchKernelGGL(fn, dim3((unsigned)nb), dim3(256), 0, s, a);
                 return hipGetLastError();
             }
