@@ -47,9 +47,16 @@ def test_generic_path(dt, cm, k, stride, pad):
 @pytest.mark.parametrize("dt,ot", [("f32", "f32"), ("bf16", "bf16")])
 @pytest.mark.parametrize("b,H,W,C,k,stride,pad", [(2, 15, 17, 24, 3, 2, 1), (1, 2, 3, 8, 3, 2, 1), (3, 8, 3, 264, 3, 2, 0),
                                                   (1, 5, 6, 40, 3, 2, 3), (9, 31, 33, 64, 5, 1, 2), (12, 41, 47, 64, 5, 2, 2),
-                                                  (9, 30, 29, 64, 5, 1, 0), (40, 3, 60, 64, 5, 1, 4), (4, 3, 4, 16, 5, 2, 2)])
-def test_window_kernel(dt, ot, b, H, W, C, k, stride, pad):
+                                                  (9, 30, 29, 64, 5, 1, 0), (40, 3, 60, 64, 5, 1, 4), (4, 3, 4, 16, 5, 2, 2),
+                                                  (16, 41, 47, 64, 5, 2, 2), (14, 30, 29, 64, 5, 1, 0), (2000, 3, 4, 64, 5, 2, 2)])
+def test_window_kernel(dt, ot, b, H, W, C, k, stride, pad, monkeypatch, capfd):
+    monkeypatch.setenv("ISAM_LOG", "1")
     _case(b, H, W, C, 12, k=k, stride=stride, pad=pad, dt=dt, ot=ot, seed=H)
+    # 5x5 layers of fewer than 121 workgroups (a thread per channel vector, column and two rows) run
+    # on the generic kernel
+    Ho, Wo = ((n + 2 * pad - k) // stride + 1 for n in (H, W))
+    threads = b * ((Ho + 1) // 2) * Wo * (C // (8 if dt == "bf16" else 4))
+    assert ("depthwise window kernel" in capfd.readouterr().err) == (k == 3 or threads > 120 * 256)
 
 
 def test_window_kernel_skips_taps_outside_the_image():
