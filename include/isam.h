@@ -75,8 +75,11 @@ typedef enum {
  * expires the tile's outputs are NaN) and adds its partial sums in a fixed
  * order, so results stay deterministic; when every workgroup of the grid is
  * resident at once, each slice instead finishes half of the tile's rows with
- * the other slice's partial sums for that half (the same sums).  Other split plans sum the slices
- * in a second kernel.  bf16 products whose tile count leaves most compute
+ * the other slice's partial sums for that half (the same sums).  Products of
+ * fewer 128x128 tiles than compute units (bf16, and fp32 as below) have their
+ * slices summed, in slice order, by the last workgroup of a tile to finish,
+ * which waits for nobody; they use as many slices as the workspace holds, at any
+ * address.  Other split plans sum the slices in a second kernel.  bf16 products whose tile count leaves most compute
  * units idle in a last partial round (A not transposed, 16-byte aligned
  * rows, workspace 256-byte aligned) run a stream-K schedule instead
  * (Section 3.4's allocation of work to processing units): a persistent grid
@@ -101,15 +104,19 @@ typedef enum {
  * runs on the element-wise tile kernel.  A workspace that overlaps A, B or C
  * is rejected.
  * Large fp32 products (A [M][K]; B [N][K], or [K][N] with N a multiple of 8;
- * M*N >= 512*(M+N); workspace 256-byte aligned and holding the copies) run on
- * the bf16 matrix cores: each operand value x is split into three bf16 terms
- * h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), copied into the start of
- * the workspace as six K blocks (12 bytes per operand value), and one bf16
- * product over K' = 6*Kp sums hh + hm + mh + hl + lh + mm in fp32: the fp32
+ * M*N >= 512*(M+N); at least one 128x128 tile per compute unit, or smaller where
+ * the kernel below does not pay; workspace 256-byte aligned and holding the
+ * copies) run on the bf16 matrix cores: each operand value x is split into three
+ * bf16 terms h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), copied into the
+ * start of the workspace as six K blocks (12 bytes per operand value), and one
+ * bf16 product over K' = 6*Kp sums mm + lh + hl + mh + hm + hh in fp32: the fp32
  * product to within the dropped terms (below 2^-23 of |a*b|).  Inputs must be
  * finite and below 3.39e38 in magnitude there (an infinite input gives NaN
  * instead of +-inf).  isam_gemm_workspace_size includes these bytes when the
- * split applies; with a smaller workspace the fp32 tile kernel runs.  The
+ * split applies; with a smaller workspace the kernels below run.
+ * Other fp32 products that are large enough form the terms in registers, eight
+ * products each (all but l*l, 2^-32 of the product), on any finite or infinite
+ * input; the rest runs on the fp32 matrix instructions.  The
  * workspace needs no initial contents; concurrent calls must not share one.
  */
 isam_status_t isam_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K,
@@ -143,7 +150,8 @@ size_t isam_gemm_workspace_size(int trans_a, int trans_b, int64_t M, int64_t N, 
  * kernel runs (3x3, stride 1, pad 1, multiplier 1; see the workspace query),
  * each fp32 product of the pointwise step is formed from a three-way bf16
  * split of both operands (six bf16 products, fp32 accumulation; the dropped
- * terms are below 2^-23 of the product).
+ * terms are below 2^-23 of the product).  Elsewhere the pointwise step is a
+ * product of isam_gemm that never uses split copies.
  */
 isam_status_t isam_dwsep_conv(int64_t batch, int64_t H, int64_t W, int64_t C_in, int64_t depth_mult,
                               int64_t kh, int64_t kw, int64_t stride, int64_t pad, int64_t C_out,

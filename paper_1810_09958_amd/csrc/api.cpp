@@ -475,11 +475,16 @@ double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, b
 // 128x128 workgroup (one per CU) and 0.21 us for a 64x64 one alone on its CU
 // (0.20 each when two share it); further rounds cost 2.5 / 1.5 us of start and
 // end each; a split into S slices 4 + 1.5 S us (128x128) or 1 + S / 2 (64x64).
-// Measured, bf16, us (ring / the plans it replaces; at 128x128 grids of at
-// least one tile per CU the three-stage ring of gemm_dma.hpp is as fast or
+// What every candidate pays alike is left out: the first start and end, 6 us for
+// 128x128 tiles and 4 for 64x64, and 1.5 to 2 to read C where it accumulates
+// (3072x1024, one slice, K = 512 / 1024 / 2048 / 4096: NT 10.0 / 13.5 / 21.2 / 35.6,
+// NN 10.3 / 14.3 / 23.2 / 38.9, TN accumulating 11.6 / 15.5 / 22.8 / 37.9).
+// Measured per call, fp32 out, us (ring / the plans it replaces; at 128x128 grids of
+// at least one tile per CU the three-stage ring of gemm_dma.hpp is as fast or
 // faster: 2048x3072x1024 NT 22 / 17.5, 2048^3 23 / 23):
-//   3072x1024x2048 TN 18.1 / 47.6, 2608x1032x4472 TN 37 / 77, 1024^3 NN 7.7 / 16.9,
-//   648x1520x3096 NT 20 / 28, 4968x128x2064 NN 12.3 / 22.5, 512x512x4096 NN 11.9 / 21.9.
+//   3072x1024x2048 TN accumulating 22-24 / 48-50, 2608x1032x4472 TN 40-42 / 80,
+//   1024^3 NN 9 / 15.7, 648x1520x3096 NT 21.7 / 28.5, 4968x128x2064 NN 13.4 / 22,
+//   512x512x4096 NN 12.7 / 21.4, 2048x1024x4096 NT 30.5 / 41.
 // ISAM_GEMM_CONFIG ring=0 switches it off, ring=1 / ring=2 force 128x128 / 64x64
 // tiles and rs=<n> the K slices; settings of the other kernels also switch it off;
 // rmix=1 (test hook) treats the slices of every tile as spread over several XCDs.
@@ -903,6 +908,8 @@ size_t align256(size_t v) { return (v + 255) & ~(size_t)255; }
 // as run_gemm's).
 size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type, bool split_copies = true) {
     const int cus = device_cus();
+    // Also where the ring kernel will run: operands whose pointers or leading dimensions
+    // are off 16 bytes, which the sizes do not show, take this plan.
     const GemmPlan p = plan_gemm(M, N, K, ab_type, cus);
     size_t ws = gemm_ws_bytes(p, M, N);
     // K slices' sums, wherever the caller's workspace starts

@@ -21,13 +21,11 @@
 //     so the form needs no co-residency and no second kernel; the counting word
 //     also collects the XCDs, and slices that ran on several (a stream with a CU
 //     mask, another partition) make the last arrival form the tile by itself.
-// Measured per call, back to back, against the plans it replaces (register-
-// staged 128x64 / 64x64 tiles, a transposing copy of A, split-K with a
-// reduction kernel): 3072x1024x2048 TN accumulating 47.7 -> 22.1 us,
-// 2608x1032x4472 TN 87.1 -> 39.9, 1024^3 NN 16.9 -> 7.9, 648x1520x3096 NT 28.0 -> 21.3,
-// 4968x128x2064 NN 22.5 -> 13.8.  Ablations on 2048x2048x8192 (75 us): MFMAs alone
-// 35 us, copies alone 47, LDS reads alone 26 (tr) to 53 (b128); 53 us on zeros, so
-// long products of random values are held by power.
+// Per call against the plans it replaces (register-staged 128x64 / 64x64 tiles, a
+// transposing copy of A, split-K with a reduction kernel): the table above plan_ring
+// in api.cpp.  Ablations on 2048x2048x8192 (75 us): MFMAs alone 35 us, copies alone
+// 47, LDS reads alone 26 (tr) to 53 (b128); 53 us on zeros, so long products of random
+// values are held by power.
 // LDS layouts and swizzles are those of the large direct-to-LDS kernel
 // (gemm_dma.hpp); rows of 64 M / N values (128 bytes) swizzle their 32-byte
 // blocks by 2 * ((k >> 1) & 1): the four K rows of a transpose read are two

@@ -21,8 +21,10 @@
 //   * one workgroup barrier per tile: at barrier i the copies of tile i have
 //     landed and every consumer has finished reading tile i-1, whose stage the
 //     producers then refill with tile i+7.
-// fp32 is bound by its matrix instructions here (32 rows x 32 columns x K = 64 take
-// 2048 cycles of a SIMD; only ceil(N / 32) of the 8 consumer waves work).  Per call,
+// fp32 spends less than half of its time in matrix instructions (a 32 x 32 block over
+// K = 64 takes 2048 cycles of a SIMD; 50176x128x64 has seven tiles per CU, 6.8 of 16 us):
+// only ceil(N / 32) of the 8 consumer waves work, one per SIMD up to N = 128, and
+// each stores a tile between its chains of MFMAs, with nothing beside it.  Per call,
 // us (this kernel / the tile kernel it replaces): 100352x64x32 15.4 / 19.3,
 // 50000x96x40 14.2 / 17.1, 12544x200x100 13.8 / 15.9, 50176x96x128 22.1 / 26.5,
 // 50176x128x64 16.7 / 17.2.
