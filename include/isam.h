@@ -79,8 +79,8 @@ typedef enum {
  * fewer 128x128 tiles than compute units (bf16, and fp32 as below) have their
  * slices summed, in slice order, by the last workgroup of a tile to finish,
  * which waits for nobody; they use as many slices as the workspace holds, at any
- * address.  Other split plans sum the slices in a second kernel.  bf16 products whose tile count leaves most compute
- * units idle in a last partial round (A not transposed, 16-byte aligned
+ * address.  Other split plans sum the slices in a second kernel.
+ * bf16 products whose tile count leaves most compute units idle in a last partial round (A not transposed, 16-byte aligned
  * rows, workspace 256-byte aligned) run a stream-K schedule instead
  * (Section 3.4's allocation of work to processing units): a persistent grid
  * sized to what the device holds at once, the workgroups of one XCD splitting
@@ -104,9 +104,9 @@ typedef enum {
  * runs on the element-wise tile kernel.  A workspace that overlaps A, B or C
  * is rejected.
  * Large fp32 products (A [M][K]; B [N][K], or [K][N] with N a multiple of 8;
- * M*N >= 512*(M+N); at least one 128x128 tile per compute unit, or smaller where
- * the kernel below does not pay; workspace 256-byte aligned and holding the
- * copies) run on the bf16 matrix cores: each operand value x is split into three
+ * M*N >= 512*(M+N); at least one 128x128 tile per compute unit, or rows off 16
+ * bytes that are not worth a copy of their own; workspace 256-byte aligned and
+ * holding the copies) run on the bf16 matrix cores: each operand value x is split into three
  * bf16 terms h = bf16(x), m = bf16(x - h), l = bf16(x - h - m), copied into the
  * start of the workspace as six K blocks (12 bytes per operand value), and one
  * bf16 product over K' = 6*Kp sums mm + lh + hl + mh + hm + hh in fp32: the fp32

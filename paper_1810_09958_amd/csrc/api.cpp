@@ -446,27 +446,29 @@ bool pack_b_needed(int trans_b, int64_t N, int64_t K, int ab_type, const void* B
 // tiles, which take 128x128 / 64x64 / 128x64 workgroups 2.3 / 0.84 / 1.2 us when
 // few CUs are busy and 3.4 / 0.98 / 1.82 when all are (power: 1.25 PFLOP/s of bf16
 // products; busy: share of the rounds' CUs that have a workgroup).
-double f32x_us(int ring, int64_t iters, int64_t wgs, int64_t sp, int cus) {
+double f32x_us(int ring, int64_t iters, int64_t wgs, int64_t per_cu, int64_t sp, int cus) {
     static const double fixed[3] = {8.5, 8.0, 9.0}, rate[3] = {2.3, 0.84, 1.2}, power[3] = {1.1, 0.14, 0.62};
-    const int64_t per_cu = cdiv(wgs, cus);
     const double busy = (double)wgs / (double)(per_cu * cus);
     const double split = sp <= 1 ? 0.0 : ring == 2 ? 0.7 + 1.6 * (double)sp : 2.5 + 1.1 * (double)sp;
     return (double)per_cu * (fixed[ring - 1] + (rate[ring - 1] + power[ring - 1] * busy * busy) * (double)iters) + split;
 }
-// The fp32 tile kernel runs at about 110 TFLOP/s (with 64x64 tiles 80 at one per CU,
-// 125 at more) over the CUs its rounds of tiles keep busy: 2048x1024x1024 45 us by
-// this model and 48 measured, 1536^3 123 / 123, 1000^3 31 / 34, 512x512x4096 33 / 37,
-// 4096x512x512 25.5 / 27.4, 8192x256x256 15.8 / 15.7, 1600x1200x400 19 / 20.  Element by
-// element it runs at about 40.
+// The fp32 tile kernel: the rounds of its tiles, each a start and end and a time per
+// 64-deep K tile by tile size (64x64 tiles alone on their CUs: by the CUs they keep busy).
+// Model / measured, us: 2048x1024x1024 46 / 48, 1536^3 126 / 123, 1000^3 36 / 34,
+// 512x512x4096 36 / 37, 4096x512x512 26 / 27, 1600x1200x400 22 / 20, 992x1736x1160 53 / 54,
+// 2064x912x3096 130 / 133, 3072x4096x1024 215 / 214, 1744x88x264 10.8 / 10.4, 820x312x100
+// 7 / 7.8.  Element by element it runs at about 40 TFLOP/s.
 double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, bool aligned, int cus) {
-    const double flops = 2.0 * (double)batch * (double)M * (double)N * (double)K;
-    if (!aligned) return 6.0 + flops / 40e6;
+    if (!aligned) return 6.0 + 2.0 * (double)batch * (double)M * (double)N * (double)K / 40e6;
     if (p.skinny || p.small) p = plan_gemm(M, N, K, kF32, cus, /*allow_skinny=*/false);
     int bm, bn, bk;
     tile_dims(p.tile, kF32, &bm, &bn, &bk);
-    const int64_t wgs = batch * cdiv(M, bm) * cdiv(N, bn) * (batch > 1 ? 1 : p.k_splits);
-    const double busy = (double)wgs / (double)(cdiv(wgs, cus) * cus);
-    return 6.0 + flops / ((bm * bn >= 128 * 64 ? 110e6 : wgs > cus ? 125e6 : 80e6) * busy);
+    const int64_t splits = batch > 1 ? 1 : p.k_splits, area = (int64_t)bm * bn;
+    const int64_t wgs = batch * cdiv(M, bm) * cdiv(N, bn) * splits, per_cu = cdiv(wgs, cus);
+    const double iters = (double)cdiv(cdiv(K, splits), 64), busy = (double)wgs / (double)cus;
+    if (area <= 64 * 64 && per_cu == 1) return std::max(7.0, 2.5 + (1.63 + 0.5 * busy * busy) * iters);
+    const double rate = area <= 64 * 64 ? 1.3 : area <= 128 * 64 ? 2.5 : area <= 128 * 128 ? 4.35 : area <= 256 * 128 ? 8.7 : 16.5;
+    return (area <= 64 * 64 ? 4.0 : 6.0) + rate * (double)per_cu * iters;
 }
 
 // bf16 products whose 128x128 tiles leave CUs idle run on the LDS-ring kernel
@@ -491,10 +493,10 @@ double f32_tile_us(GemmPlan p, int64_t M, int64_t N, int64_t K, int64_t batch, b
 //
 // fp32 products take the same tiles and K slices on the kernel of gemm_f32x.hpp
 // (ISAM_GEMM_CONFIG f32x= instead of ring=), at any grid size, where that beats the
-// tile kernel's plan p.  room: workspace bytes that may hold the slices' sums (as many
-// slices as fit; 0: none).
+// tile kernel's plan p or `always`.  room: workspace bytes that may hold the slices'
+// sums (as many slices as fit; 0: none).
 RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_type, bool aligned, int64_t batch, int cus,
-                   size_t room) {
+                   size_t room, bool always = false) {
     RingPlan none{0, 1, 0};
     if (M <= 0 || N <= 0 || K <= 0) return none;
     const bool f32 = ab_type == kF32;
@@ -511,9 +513,10 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
     }
     // What the fp32 kernel has to beat (operands off 16 bytes are copied first: a launch
     // and about 3 TB/s).
-    const double beat = f32 && !force ? 0.95 * f32_tile_us(p, M, N, K, batch, aligned, cus) -
+    const bool weigh = f32 && !force && !always;
+    const double beat = weigh ? 0.95 * f32_tile_us(p, M, N, K, batch, aligned, cus) -
                                             (aligned ? 0.0 : 4.0 + 8.0 * (double)(M + N) * (double)K / 3e6) : 0.0;
-    if (f32 && !force && f32x_us(2, 1, 1, 1, cus) >= beat) return none;  // not even at its least
+    if (weigh && f32x_us(2, 1, 1, 1, 1, cus) >= beat) return none;  // not even at its least
     if (!f32 && !force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
     RingPlan best = none;
     double best_us = 0;
@@ -527,7 +530,7 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
         for (int64_t sp = 1; sp <= most; ++sp) {
             if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
             const int64_t iters = cdiv(nk, sp), wgs = tiles * cdiv(nk, iters), per_cu = cdiv(wgs, cus);
-            const double us = f32 ? f32x_us(ring, iters, wgs, sp, cus) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
+            const double us = f32 ? f32x_us(ring, iters, wgs, per_cu, sp, cus) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
                                         : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
                                               (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);
             if (!best.ring || us < best_us) {
@@ -536,7 +539,7 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
             }
         }
     }
-    if (f32 && !force && best_us >= beat) return none;
+    if (weigh && best_us >= beat) return none;
     return best;
 }
 
@@ -614,17 +617,17 @@ size_t slice_room(const void* ws, size_t bytes, size_t used) {
 }
 
 // Whether a product that could run on split copies of its operands (split_plan) takes
-// the kernel that forms the terms in registers instead: small grids where its plan
-// pays, with operands that are aligned or can be copied into the workspace.
-// Otherwise the split copies keep it, which take any alignment.
-bool f32x_over_split(const GemmPlan& p, int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a,
-                     bool need_b, const void* ws, size_t bytes, int cus) {
+// the kernel that forms the terms in registers instead: grids below the chip's size,
+// where it is faster (992x1736x1160 42 us, split copies 59, tile kernel 54; 1488x1272x800 32 / 45 / 37)
+// or level (1032x872x264 14.2 / 15.5 / 15.4), with operands that are aligned or can be
+// copied into the workspace.  Otherwise the split copies keep it, which take any
+// alignment.
+bool f32x_over_split(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, bool need_a, bool need_b, size_t bytes,
+                     int cus) {
     if (!f32x_grid(M, N, cus)) return false;
     const RingPack k = ring_pack(trans_a, trans_b, M, N, K, kF32, need_a, need_b);
     const size_t copies = k.a_bytes + k.b_bytes;
-    if (copies && (copies > bytes || !ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k))) return false;
-    const size_t room = bytes == kAnyRoom ? kAnyRoom : slice_room(ws, bytes, copies);
-    return plan_ring(p, M, N, K, kF32, !need_a && !need_b, 1, cus, room).ring != 0;
+    return !copies || (copies <= bytes && ring_pack_pays(trans_a, trans_b, M, N, K, kF32, cus, k));
 }
 
 isam_status_t validate_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int ab_type,
@@ -678,13 +681,14 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
         p.sk = 0;
     }
     p.vec = (K == 0) ? 1 : (vec_ok(trans_a, trans_b, M, N, K, ab_type, A, lda, B, ldb) ? 1 : 0);
+    bool terms = false;  // on bf16 terms formed in registers, whatever the tile kernel would take
     if (ab_type == kF32 && batch == 1 && K > 0 && split_copies) {
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         char* ws = static_cast<char*>(workspace);
         const size_t split_bytes = k.a_bytes + k.b_bytes;
-        if (k.pays && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes &&
-            !f32x_over_split(p, trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
-                             pack_b_needed(trans_b, N, K, ab_type, B, ldb), ws, workspace_bytes, device_cus())) {
+        terms = k.pays && f32x_over_split(trans_a, trans_b, M, N, K, pack_a_needed(trans_a, M, K, ab_type, A, lda),
+                                          pack_b_needed(trans_b, N, K, ab_type, B, ldb), workspace_bytes, device_cus());
+        if (k.pays && !terms && ws && ((uintptr_t)ws & 255) == 0 && workspace_bytes >= split_bytes) {
             const int64_t es = (int64_t)dsize(ab_type);
             const size_t a_b = (size_t)(((M - 1) * lda + K) * es);
             const size_t b_b = (size_t)((trans_b ? (N - 1) * ldb + K : (K - 1) * ldb + N) * es);
@@ -724,7 +728,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                                          ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k));
             const RingPlan r = !fits ? RingPlan{0, 1, 0}
                                      : plan_ring(p, M, N, K, ab_type, !need_a && !need_b, batch, cus,
-                                                 batch == 1 ? slice_room(ws, workspace_bytes, pack_bytes) : 0);
+                                                 batch == 1 ? slice_room(ws, workspace_bytes, pack_bytes) : 0, terms);
             if (r.ring) {
                 const size_t sums = gemm_ring_ws_bytes(r, M, N), sums_at = slice_offset(ws, pack_bytes);
                 const size_t used = sums ? sums_at + sums : pack_bytes;
@@ -922,22 +926,23 @@ size_t gemm_query(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K, int
     // them, and what the packed product then uses.
     const int64_t E = ab_type == ISAM_BF16 ? 8 : 4;
     const bool a_off = (trans_a ? M : K) % E != 0, b_off = (trans_b ? K : N) % E != 0;
+    bool terms = false;  // as in run_gemm
     if (ab_type == ISAM_F32 && split_copies) {
         const SplitPlan k = split_plan(trans_a, trans_b, M, N, K);
         if (k.pays) {
             // Split copies, or the kernel that forms the terms in registers and, as the
             // split copies take operands of any alignment, room for copies of both.
             const RingPack both = ring_pack(trans_a, trans_b, M, N, K, kF32, true, true);
-            if (!f32x_over_split(p, trans_a, trans_b, M, N, K, a_off, b_off, nullptr, kAnyRoom, cus) ||
-                !f32x_over_split(p, trans_a, trans_b, M, N, K, true, true, nullptr, kAnyRoom, cus))
+            if (!f32x_over_split(trans_a, trans_b, M, N, K, true, true, kAnyRoom, cus))
                 ws = std::max(ws, k.a_bytes + k.b_bytes + gemm_ws_bytes(plan_gemm(M, N, 6 * k.Kp, kBF16, cus), M, N));
             else
-                ws = std::max(ws, both.a_bytes + both.b_bytes + sums(plan_ring(p, M, N, K, kF32, false, 1, cus, kAnyRoom)));
+                ws = std::max(ws, both.a_bytes + both.b_bytes + sums(plan_ring(p, M, N, K, kF32, false, 1, cus, kAnyRoom, true)));
+            terms = f32x_over_split(trans_a, trans_b, M, N, K, a_off, b_off, kAnyRoom, cus);
             if (!f32x_grid(M, N, cus)) return ws;
         }
     }
     {
-        const RingPlan r = plan_ring(p, M, N, K, ab_type, !a_off && !b_off, 1, cus, kAnyRoom);
+        const RingPlan r = plan_ring(p, M, N, K, ab_type, !a_off && !b_off, 1, cus, kAnyRoom, terms);
         if (r.ring && !special_kernel(p, trans_a, trans_b, M, N, K, ab_type, !a_off && !b_off, K % E == 0, cus)) {
             const RingPack k = ring_pack(trans_a, trans_b, M, N, K, ab_type, a_off, b_off);
             if (!(k.a || k.b) || ring_pack_pays(trans_a, trans_b, M, N, K, ab_type, cus, k))
