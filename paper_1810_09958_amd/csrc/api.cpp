@@ -518,6 +518,7 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
                                             (aligned ? 0.0 : 4.0 + 8.0 * (double)(M + N) * (double)K / 3e6) : 0.0;
     if (weigh && f32x_us(2, 1, 1, 1, 1, cus) >= beat) return none;  // not even at its least
     if (!f32 && !force && batch * cdiv(M, 128) * cdiv(N, 128) >= cus) return none;
+    const int xcds = cus % 32 == 0 ? cus / 32 : 1;  // as the launch
     RingPlan best = none;
     double best_us = 0;
     for (int ring = 1; ring <= (f32 ? 3 : 2); ++ring) {
@@ -529,7 +530,11 @@ RingPlan plan_ring(const GemmPlan& p, int64_t M, int64_t N, int64_t K, int ab_ty
         while (most > 1 && gemm_ring_ws_bytes(RingPlan{ring, (int)most, 0}, M, N) > room) --most;
         for (int64_t sp = 1; sp <= most; ++sp) {
             if (force_s && sp != std::min<int64_t>(force_s, most)) continue;
-            const int64_t iters = cdiv(nk, sp), wgs = tiles * cdiv(nk, iters), per_cu = cdiv(wgs, cus);
+            // The XCDs take equal numbers of whole tiles, slices and all, so a full one may
+            // need a round more than the average (84 tiles in three slices: 33 workgroups on
+            // 32 CUs, 50 us for the 36 of two slices).
+            const int64_t iters = cdiv(nk, sp), slices = cdiv(nk, iters), wgs = tiles * slices;
+            const int64_t per_cu = cdiv(batch * cdiv(cdiv(M, bm) * cdiv(N, bn), xcds) * slices, cus / xcds);
             const double us = f32 ? f32x_us(ring, iters, wgs, per_cu, sp, cus) : ring == 1 ? 0.47 * (double)(iters * per_cu) + 2.5 * (double)(per_cu - 1) + (sp > 1 ? 4.0 + 1.5 * (double)sp : 0.0)
                                         : (double)iters * (per_cu == 1 ? 0.21 : 0.20 * (double)per_cu) + 1.5 * (double)((per_cu - 1) / 2) +
                                               (sp > 1 ? 1.0 + 0.5 * (double)sp : 0.0);

@@ -83,6 +83,21 @@ def test_f32x_planned(ta, tb, M, N, K, monkeypatch):
     assert bool(((y.reshape(-1, 384) - ref).abs() <= _tol(5 * 256) * S).all())
 
 
+# An XCD runs whole tiles with all their slices: a plan may not give a full one more rounds of
+# workgroups than the chip has on average (84 tiles of 64x64 in three slices did: 33 on 32 CUs).
+@pytest.mark.parametrize("M,N,K,ta,tb", [(128, 2688, 3456, 0, 1), (2600, 68, 3232, 1, 0), (1536, 768, 3072, 1, 0), (200, 2000, 4000, 1, 0)])
+def test_f32x_plan_counts_rounds_per_xcd(M, N, K, ta, tb, monkeypatch, capfd):
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("counts for 8 XCDs of 32 CUs")
+    monkeypatch.delenv("ISAM_GEMM_CONFIG", raising=False)
+    monkeypatch.setenv("ISAM_LOG", "1")
+    _check(*_operands(M, N, K, ta, tb, 0, K), ta, tb)
+    plan = capfd.readouterr().err.split("ring kernel: ")[1]
+    bm, bn = (int(x) for x in plan.split(" ")[0].split("x"))
+    slices, tiles = int(plan.split(" K slices")[0].split(" ")[-1]), -(-M // bm) * -(-N // bn)
+    assert -(-(-(-tiles // 8) * slices) // 32) == -(-tiles * slices // 256)
+
+
 # Products that the split copies (any alignment) served: with bases and leading dimensions off 16
 # bytes and the queried workspace they run on the terms too, not element by element.
 @pytest.mark.parametrize("tb", [0, 1])
