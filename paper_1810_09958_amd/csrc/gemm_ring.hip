@@ -44,9 +44,12 @@ hipError_t ring_args(const GemmArgs& a, const RingPlan& r, const RingPadded& pad
     t.splits = (int)((a.K + t.k_per_split - 1) / t.k_per_split);  // no slice is empty
     // K tiles per fold: about half the root of a slice's K tiles makes the two chains of
     // additions equal; fewer than four cost time and gain nothing over the plans that
-    // cut K into more slices.
+    // cut K into more slices.  Up to K = 4096, 128x128 tiles stand in for plans of one
+    // slice, whose error they have in one chain of up to 2048 of K (3072x1024x2048 TN
+    // accumulating 22.2 us, 22.8 with folds).
     t.fold = 4;
     while (4 * t.fold * t.fold < t.k_per_split / 64) t.fold += 2;
+    if (r.ring == 1 && a.K < 4096 && t.k_per_split <= 2048) t.fold = 32;
     if (t.splits > 255 || (t.splits > 1 && ((uintptr_t)a.partial & 255))) return hipErrorInvalidValue;
     const int64_t a_rows = a.trans_a ? a.K : a.M, a_cols = a.trans_a ? a.M : a.K;
     const int64_t b_rows = a.trans_b ? a.N : a.K, b_cols = a.trans_b ? a.K : a.N;

@@ -89,7 +89,7 @@ def test_ring_unaligned_operands(ta, tb, room, monkeypatch):
 # short last one.
 @pytest.mark.parametrize("M,N,K,ta,tb", [(2608, 1032, 4472, 1, 0), (2048, 1024, 4096, 0, 1), (1024, 2048, 8192, 0, 0),
                                          (512, 512, 16384, 0, 0), (64, 960, 1024, 1, 0), (568, 208, 936, 1, 0),
-                                         (144, 3864, 4152, 0, 0)])
+                                         (144, 3864, 4152, 0, 0), (3072, 1024, 2048, 1, 0), (2304, 1408, 3080, 0, 0)])
 def test_ring_error_is_no_larger_than_with_more_slices(M, N, K, ta, tb, monkeypatch):
     g = torch.Generator(device="cuda").manual_seed(K)
     A = torch.randn((K, M) if ta else (M, K), device="cuda", generator=g).bfloat16()
