@@ -823,7 +823,7 @@ isam_status_t run_gemm(int trans_a, int trans_b, int64_t M, int64_t N, int64_t K
                                                          true, cus, stream);
                 if (e != hipSuccess) return hip_fail(e, who);
                 return run_gemm(k.trans_a, k.trans_b, M, N, k.Kp, ab_type, Ap, ldap, Bp, ldbp, accumulate, c_type, C,
-                                ldc, bias, ws + pack_bytes, workspace_bytes - pack_bytes, stream, who);
+                                ldc, bias, ws + pack_bytes, workspace_bytes - pack_bytes, stream, who, 1, 0, 0, 0, split_copies);
             }
         }
     }

@@ -69,16 +69,18 @@ def test_window_kernel_skips_taps_outside_the_image():
         assert not bool(torch.isfinite(y[:, -1, -1]).any())
 
 
-def test_unfused_fp32_infinite_pixel_and_rounding():
+@pytest.mark.parametrize("Co", [1024, 1022])
+def test_unfused_fp32_infinite_pixel_and_rounding(Co):
     # A pointwise product large enough for split copies of its operands, which it must not take (an
     # infinity splits into infinity and NaN): infinite outputs under an infinite pixel, and where
-    # one product makes an output, that product rounded once.
-    x, D, P = torch.randn(6, 56, 56, 512, device="cuda"), torch.zeros(3, 3, 512, 1, device="cuda"), torch.randn(512, 1024, device="cuda")
+    # one product makes an output, that product rounded once; also with room for such copies, and
+    # where the weights are copied into aligned rows first.
+    x, D, P = torch.randn(6, 56, 56, 512, device="cuda"), torch.zeros(3, 3, 512, 1, device="cuda"), torch.randn(512, Co, device="cuda")
     D[1, 1] = 1.0
     x[..., 1:] = 0.0
     x[2, 10, 12, 0] = float("inf")
     for room in (0, 1 << 28):
-        ws = torch.empty(isam.dwsep_conv_workspace_size(6, 56, 56, 512, 1, 3, 3, 2, 1, 1024, 0, 0) + room, device="cuda", dtype=torch.uint8)
+        ws = torch.empty(isam.dwsep_conv_workspace_size(6, 56, 56, 512, 1, 3, 3, 2, 1, Co, 0, 0) + room, device="cuda", dtype=torch.uint8)
         y = isam.dwsep_conv(x, D, P, stride=2, pad=1, workspace=ws)
         assert bool((y[2, 5, 6] == torch.where(P[0] > 0, 1, -1) * float("inf")).all())
         y[2, 5, 6] = 0.0
